@@ -42,7 +42,7 @@ WORKLOAD = "bert_base_l12_d768_s128"
 # misses, which the 256 MB MALL may serve without touching HBM.  Valid only for the GEMM
 # source and build flags they were counted on; any other source reports null.
 FFN2_TRAFFIC = {"source_sha256_16": "18608253d3f3474f", "bytes": (37120.6 * 2.0 + 13292.1 * 1.0) * 1024}
-GEMM_SOURCES = ("paper_2503_05130_amd/csrc/gemm.hip", "paper_2503_05130_amd/csrc/gemm.h",
+GEMM_SOURCES = ("paper_2503_05130_amd/csrc/gemm.hip", "paper_2503_05130_amd/csrc/gemm.h", "paper_2503_05130_amd/csrc/gemm_device.h",
                 "paper_2503_05130_amd/csrc/launch.h", "paper_2503_05130_amd/csrc/gelu.h",
                 "paper_2503_05130_amd/build.py")
 
