@@ -7,7 +7,7 @@
 //   ln_head   : fp32 [rows, d] -> LN -> per-token head, fp32 logits [rows, n_out]
 //               (the model's last LN fused with its classifier, so the final
 //               hidden states never go back to HBM)
-// Plus the fp32 -> bf16 cast of a post-LN model's input and the CU residency probe.
+// Plus the fp32 -> bf16 cast of a post-LN model's input, an fp32 copy and the CU residency probe.
 #include "kernels.h"
 
 namespace iefwd {
@@ -146,6 +146,15 @@ __global__ __launch_bounds__(256) void cast_bf16_kernel(const float *__restrict_
     reinterpret_cast<u32x2 *>(y)[i] = u32x2{pack2(v[0], v[1]), pack2(v[2], v[3])};
 }
 
+// fp32 copy between device buffers, or between one and pinned host memory.
+// 16-byte accesses where both addresses allow it.
+__global__ __launch_bounds__(256) void copy_f32_kernel(const float *__restrict__ src, float *__restrict__ dst,
+                                                       size_t n, size_t n4) {
+    const size_t i = (size_t)blockIdx.x * 256 + threadIdx.x;
+    if (i < n4) reinterpret_cast<f32x4 *>(dst)[i] = reinterpret_cast<const f32x4 *>(src)[i];
+    else if (4 * n4 + (i - n4) < n) dst[4 * n4 + (i - n4)] = src[4 * n4 + (i - n4)];
+}
+
 // s_getreg immediates: register id | (offset << 6) | ((size - 1) << 11)
 constexpr int kHwRegHwId = 4 | (0 << 6) | (31 << 11);    // HW_ID: wave/SIMD/CU/SH/SE fields
 constexpr int kHwRegXccId = 20 | (0 << 6) | (31 << 11);  // XCC_ID
@@ -213,6 +222,14 @@ hipError_t launch_cast_bf16(const float *x, bf16_t *y, size_t n, hipStream_t str
     const size_t n4 = n / 4;
     const dim3 grid((unsigned)((n4 + 255) / 256)), block(256);
     return launch_kernel(cast_bf16_kernel, grid, block, stream, x, y, n4);
+}
+
+hipError_t launch_copy_f32(const float *src, float *dst, size_t n, hipStream_t stream) {
+    if (n == 0) return hipSuccess;
+    // vectors first, then single elements: the last n % 4, or all of them
+    const bool aligned = (reinterpret_cast<uintptr_t>(src) | reinterpret_cast<uintptr_t>(dst)) % 16 == 0;
+    const size_t n4 = aligned ? n / 4 : 0, threads = n4 + (n - 4 * n4);
+    return launch_kernel(copy_f32_kernel, dim3((unsigned)((threads + 255) / 256)), dim3(256), stream, src, dst, n, n4);
 }
 
 hipError_t launch_cu_probe(uint32_t *out, int n_groups, hipStream_t stream) {
