@@ -85,9 +85,11 @@ typedef struct iefwd_config {
     uint32_t pre_ln;        /* 0 = post-LN (BERT-style), 1 = pre-LN + final LN */
     uint32_t causal;        /* 0 = bidirectional, 1 = causal mask */
     uint32_t kv_cache;      /* 1 = keep every layer's K and V for iefwd_decode (needs pre_ln = causal
-                               = 1 and max_seq <= 8192), and a packed copy of the four weight
+                               = 1 and max_seq <= 8192), and packed copies of the four weight
                                matrices per layer for the decode step (the weights' device memory
-                               roughly doubles); 0 = prefill only (default) */
+                               roughly doubles; up to four times it from max_batch = 9 on, whose
+                               larger decode batches read copies of their own); 0 = prefill only
+                               (default) */
     float    ln_eps;        /* LayerNorm epsilon (default 1e-5) */
     float    w_std;         /* std of weight matrices (default 0.02) */
     float    b_std;         /* std of biases (default 0: biases are zero) */
@@ -476,7 +478,7 @@ int iefwd_test_gemm_skinny(uint32_t epilogue, const void *a, const void *w, cons
  *   r = l % 16, c = l / 16, f = b * (16 / groups) + r % (16 / groups),
  *   k = (r / (16 / groups)) * (K / groups) + 32 s + 8 c,
  * so that each wave load instruction of the product reads 1 KB of
- * consecutive addresses.  Instances created with kv_cache = 1 keep such a copy
+ * consecutive addresses.  Instances created with kv_cache = 1 keep such copies
  * of their four matrices per layer. */
 int iefwd_test_skinny_pack(const void *w, void *dst, uint32_t N, uint32_t K, uint32_t groups, void *stream);
 

@@ -315,7 +315,7 @@ __device__ inline float row_sum(float v) {
 // (bias, residual rows) and, without the LayerNorm prologue, the activations
 // are requested before the weights, so that no load is left to start after
 // the weight stream has ended.
-constexpr int kSkinnyWaves = 8, kSkinnyUnroll = 8;
+constexpr int kSkinnyWaves = 8, kSkinnyUnroll = 8;   // waves: 16 for narrow products of 9-16 rows (skinny_waves)
 constexpr int kSkinnyLnElems = 16384;
 constexpr int kSkinnyCus = 256;              // MI355X compute units
 
@@ -328,16 +328,21 @@ constexpr int kSkinnyCus = 256;              // MI355X compute units
 // writes y = fma(gamma, (z - mean) * rstd, beta), rounded to bf16, into the
 // activation tile.  NVL = K / 256 rounded up to 8 or 16 (K <= 4096).
 // finish() contains one barrier, reached by every wave.
-template <int NVL>
+// TWO (M > 8): the wave's second row is requested with the first, ahead of the
+// weights; requested after them it would arrive when the weight stream ends.
+// Rows of the activation tile are K + 8 elements apart, so that the 16 rows a
+// fragment read touches lie in distinct banks (16 rows x 1024: QKV and FFN-up
+// of 1024 x 3072 and 1024 x 4096 together 14.5 -> 12.9 us with the packed copy).
+template <int NVL, bool TWO>
 struct SkinnyLn {
     static constexpr int GBV = NVL * 64 / (64 * kSkinnyWaves);   // gamma / beta vectors per thread
-    f32x4 v[NVL];
+    f32x4 v[NVL], v2[TWO ? NVL : 1];
     f32x4 g[GBV], b[GBV];
 
     // Every vector of the row is loaded (indices clamped into the row; the
     // extra vectors are never used), so that the wait for them does not wait
     // for the weights.
-    __device__ void load_row(const GemmParams &p, int r, int lane) {
+    __device__ static void load_row(const GemmParams &p, f32x4 (&v)[NVL], int r, int lane) {
         const f32x4 *zr = reinterpret_cast<const f32x4 *>(p.lnin.z + (size_t)r * p.K);
 #pragma unroll
         for (int c = 0; c < NVL; ++c) v[c] = zr[min(c * 64 + lane, p.K / 4 - 1)];
@@ -350,7 +355,12 @@ struct SkinnyLn {
             g[j] = reinterpret_cast<const f32x4 *>(p.lnin.gamma)[i];
             b[j] = reinterpret_cast<const f32x4 *>(p.lnin.beta)[i];
         }
-        if (wave < p.M) load_row(p, wave, lane);
+        if constexpr (TWO) {
+            load_row(p, v, wave, lane);   // M > 8: every wave has a first row
+            load_row(p, v2, min(wave + kSkinnyWaves, p.M - 1), lane);
+        } else if (wave < p.M) {
+            load_row(p, v, wave, lane);
+        }
     }
 
     __device__ void finish(const GemmParams &p, bf16_t *a_lds, float *gb_lds, int tid, int lane, int wave) {
@@ -366,7 +376,7 @@ struct SkinnyLn {
             }
         }
         float mean = 0.f, rstd = 0.f;
-        auto stats = [&] {
+        auto stats = [&](const f32x4 (&v)[NVL]) {
             float sum = 0.f;
 #pragma unroll
             for (int c = 0; c < NVL; ++c)
@@ -385,7 +395,7 @@ struct SkinnyLn {
         };
         // gamma and beta of two vectors read before either is used (indices
         // clamped: unused past the row)
-        auto emit = [&](int r) {
+        auto emit = [&](const f32x4 (&v)[NVL], int r) {
 #pragma unroll
             for (int c = 0; c < NVL; c += 2) {
                 f32x4 gg[2], bb[2];
@@ -403,19 +413,20 @@ struct SkinnyLn {
 #pragma unroll
                         for (int e = 0; e < 4; ++e)
                             y[e] = __builtin_fmaf(gg[h][e], (v[c + h][e] - mean) * rstd, bb[h][e]);
-                        *reinterpret_cast<u32x2 *>(a_lds + (size_t)r * p.K + 4 * i) =
+                        *reinterpret_cast<u32x2 *>(a_lds + (size_t)r * (p.K + 8) + 4 * i) =
                             u32x2{pack2(y[0], y[1]), pack2(y[2], y[3])};
                     }
                 }
             }
         };
-        if (wave < p.M) stats();
+        if (TWO || wave < p.M) stats(v);
         __syncthreads();                      // gamma and beta staged
-        if (wave < p.M) emit(wave);
-        if (wave + kSkinnyWaves < p.M) {
-            load_row(p, wave + kSkinnyWaves, lane);
-            stats();
-            emit(wave + kSkinnyWaves);
+        if (TWO || wave < p.M) emit(v, wave);
+        if constexpr (TWO) {
+            if (wave + kSkinnyWaves < p.M) {
+                stats(v2);
+                emit(v2, wave + kSkinnyWaves);
+            }
         }
     }
 };
@@ -423,15 +434,17 @@ struct SkinnyLn {
 // NVL: 0 = activations from a; 8 or 16 = LayerNorm prologue for K <= 2048 / 4096.
 // FRAG: p.w is the packed copy of W (skinny_pack) for this G.  U: K steps a
 // wave requests at once (skinny_unroll: the wave's share of the steps, up to 8).
-template <Epi EPI, int G, int NVL, bool FRAG, int U>
-__global__ __launch_bounds__(64 * kSkinnyWaves) void skinny_kernel(GemmParams p) {
+// NW: waves (skinny_waves).  TWO: 9-16 rows with the LayerNorm prologue.
+template <Epi EPI, int G, int NVL, bool FRAG, int U, int NW, bool TWO>
+__global__ __launch_bounds__(64 * NW) void skinny_kernel(GemmParams p) {
     constexpr bool LNA = NVL > 0;
-    constexpr int NW = kSkinnyWaves;
+    static_assert(!LNA || NW == kSkinnyWaves, "the prologue's row split");
     constexpr int FPW = 16 / G, TPW = 16 / G;      // features and token columns per K-group
     constexpr int kPartBytes = (NW - 1) * 64 * 16;
     // the LayerNorm prologue's bf16 activation tile, later the waves' partial
     // sums; the prologue's gamma and beta (fp32, K each) in an array of their own
-    constexpr int kLdsBytes = LNA && kSkinnyLnElems * 2 > kPartBytes ? kSkinnyLnElems * 2 : kPartBytes;
+    constexpr int kLnBytes = (kSkinnyLnElems + 16 * 8) * 2;
+    constexpr int kLdsBytes = LNA && kLnBytes > kPartBytes ? kLnBytes : kPartBytes;
     __shared__ __attribute__((aligned(16))) char lds[kLdsBytes];
     __shared__ __attribute__((aligned(16))) float gb_lds[LNA ? 2 * NVL * 256 : 4];
     f32x4 (*part)[64] = reinterpret_cast<f32x4 (*)[64]>(lds);
@@ -447,7 +460,7 @@ __global__ __launch_bounds__(64 * kSkinnyWaves) void skinny_kernel(GemmParams p)
     constexpr int WSTEP = FRAG ? 512 : 32;
     const bf16_t *wrow = FRAG ? p.w + (size_t)blockIdx.x * steps * 512 + lane * 8
                               : p.w + (size_t)wf_row * p.K + grp * kg + chunk * 8;
-    const bf16_t *arow = (LNA ? a_lds : p.a) + (size_t)a_row * p.K + grp * kg + chunk * 8;
+    const bf16_t *arow = (LNA ? a_lds : p.a) + (size_t)a_row * (LNA ? p.K + 8 : p.K) + grp * kg + chunk * 8;
     f32x4 acc = {0.f, 0.f, 0.f, 0.f};
     // The epilogue's operands are fetched first.  Lane (fq, t) of wave 0
     // stores features n0 + 4 fq .. + 3 of token t (see below); every lane
@@ -483,7 +496,7 @@ __global__ __launch_bounds__(64 * kSkinnyWaves) void skinny_kernel(GemmParams p)
     if constexpr (LNA) {
         // the LayerNorm inputs first, then the weights; the activations are
         // normalised while the weights stream in
-        SkinnyLn<NVL> ln;
+        SkinnyLn<NVL, TWO> ln;
         ln.load(p, threadIdx.x, lane, wave);
         __builtin_amdgcn_sched_barrier(0);     // keep these loads ahead of the weights' (in-order returns)
         load_w(wave);
@@ -556,16 +569,13 @@ __global__ __launch_bounds__(64 * kSkinnyWaves) void skinny_kernel(GemmParams p)
     }
 }
 
-template <int G, int NVL, bool FRAG, int U>
+template <int G, int NVL, bool FRAG, int U, int NW, bool TWO>
 hipError_t launch_skinny(Epi epi, const GemmParams &p, hipStream_t stream) {
-    const dim3 grid(p.N / (16 / G)), block(64 * kSkinnyWaves);
+    const dim3 grid(p.N / (16 / G)), block(64 * NW);
     switch (epi) {
-    case Epi::BiasBf16: return launch_kernel(skinny_kernel<Epi::BiasBf16, G, NVL, FRAG, U>, grid, block, stream, p);
-    case Epi::BiasGeluBf16:
-        return launch_kernel(skinny_kernel<Epi::BiasGeluBf16, G, NVL, FRAG, U>, grid, block, stream, p);
-    case Epi::BiasResidF32:
-        return launch_kernel(skinny_kernel<Epi::BiasResidF32, G, NVL, FRAG, U>, grid, block, stream, p);
-    case Epi::Qkv: return launch_kernel(skinny_kernel<Epi::Qkv, G, NVL, FRAG, U>, grid, block, stream, p);
+#define EPI(E) case E: return launch_kernel(skinny_kernel<E, G, NVL, FRAG, U, NW, TWO>, grid, block, stream, p);
+    EPI(Epi::BiasBf16) EPI(Epi::BiasGeluBf16) EPI(Epi::BiasResidF32) EPI(Epi::Qkv)
+#undef EPI
     case Epi::BiasLnResidF32:
     case Epi::F32:
     case Epi::GeluBwdBf16: break;
@@ -573,31 +583,52 @@ hipError_t launch_skinny(Epi epi, const GemmParams &p, hipStream_t stream) {
     return hipErrorInvalidValue;
 }
 
+// Waves of a workgroup.  With one K-group (9-16 rows) a narrow product has few
+// workgroups (N / 16), each of which must pull its weights alone: 16 waves have
+// twice the requests in flight.  Wider than 2048 the workgroups fill the chip
+// and 8 waves leave room for the next one.  (16 rows x 4096 -> 1024: 11.1 -> 8.2
+// us with the packed copy; 1024 -> 1024 takes 4.6 us either way.)  Part of the summation
+// order, so it depends on N, K and the number of groups alone.
+int skinny_waves(int N, int K, int G, bool ln) {
+    return G == 1 && !ln && N / 16 <= kSkinnyCus / 2 && K >= 2048 ? 16 : kSkinnyWaves;
+}
+
 // K steps a wave requests at once: its share of the product's steps, rounded
 // up to a power of two, at most kSkinnyUnroll (more steps take more rounds)
-int skinny_unroll(int K, int G) {
-    const int per_wave = (K / G / 32 + kSkinnyWaves - 1) / kSkinnyWaves;
+int skinny_unroll(int K, int G, int waves) {
+    const int per_wave = (K / G / 32 + waves - 1) / waves;
     int u = 1;
     while (u < per_wave && u < kSkinnyUnroll) u *= 2;
     return u;
 }
 
-template <int G, int NVL, bool FRAG>
+template <int G, int NVL, bool FRAG, int NW, bool TWO>
 hipError_t launch_skinny_u(Epi epi, const GemmParams &p, hipStream_t stream) {
-    switch (skinny_unroll(p.K, G)) {
-    case 1: return launch_skinny<G, NVL, FRAG, 1>(epi, p, stream);
-    case 2: return launch_skinny<G, NVL, FRAG, 2>(epi, p, stream);
-    case 4: return launch_skinny<G, NVL, FRAG, 4>(epi, p, stream);
-    default: return launch_skinny<G, NVL, FRAG, 8>(epi, p, stream);
+    switch (skinny_unroll(p.K, G, NW)) {
+    case 1: return launch_skinny<G, NVL, FRAG, 1, NW, TWO>(epi, p, stream);
+    case 2: return launch_skinny<G, NVL, FRAG, 2, NW, TWO>(epi, p, stream);
+    case 4: return launch_skinny<G, NVL, FRAG, 4, NW, TWO>(epi, p, stream);
+    default: return launch_skinny<G, NVL, FRAG, 8, NW, TWO>(epi, p, stream);
     }
+}
+
+template <int G, int NVL, bool FRAG>
+hipError_t launch_skinny_v(Epi epi, const GemmParams &p, hipStream_t stream) {
+    if constexpr (G == 1 && NVL == 0) {
+        if (skinny_waves(p.N, p.K, G, false) == 16) return launch_skinny_u<G, NVL, FRAG, 16, false>(epi, p, stream);
+    }
+    if constexpr (G == 1 && NVL == 8) {   // more than 8 rows have one K-group, and K <= 16384 / 9
+        if (p.M > 8) return launch_skinny_u<G, NVL, FRAG, kSkinnyWaves, true>(epi, p, stream);
+    }
+    return launch_skinny_u<G, NVL, FRAG, kSkinnyWaves, false>(epi, p, stream);
 }
 
 template <int NVL>
 hipError_t launch_skinny_g(Epi epi, const GemmParams &p, int g, bool frag, hipStream_t stream) {
     switch (g) {
-    case 1: return frag ? launch_skinny_u<1, NVL, true>(epi, p, stream) : launch_skinny_u<1, NVL, false>(epi, p, stream);
-    case 2: return frag ? launch_skinny_u<2, NVL, true>(epi, p, stream) : launch_skinny_u<2, NVL, false>(epi, p, stream);
-    case 4: return frag ? launch_skinny_u<4, NVL, true>(epi, p, stream) : launch_skinny_u<4, NVL, false>(epi, p, stream);
+    case 1: return frag ? launch_skinny_v<1, NVL, true>(epi, p, stream) : launch_skinny_v<1, NVL, false>(epi, p, stream);
+    case 2: return frag ? launch_skinny_v<2, NVL, true>(epi, p, stream) : launch_skinny_v<2, NVL, false>(epi, p, stream);
+    case 4: return frag ? launch_skinny_v<4, NVL, true>(epi, p, stream) : launch_skinny_v<4, NVL, false>(epi, p, stream);
     }
     return hipErrorInvalidValue;
 }

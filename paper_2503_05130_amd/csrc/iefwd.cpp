@@ -136,9 +136,9 @@ struct LayerWeights {
     bf16_t *wqkv, *bqkv, *wo, *bo, *w1, *b1, *w2, *b2;   // matrices output-major [out, in]
     float *g1, *be1, *g2, *be2;
     // decode instances: packed copies of wqkv, wo, w1, w2 for the skinny
-    // product, and the K-group count each copy is packed for
-    bf16_t *packed[4] = {nullptr, nullptr, nullptr, nullptr};
-    int packed_groups[4] = {0, 0, 0, 0};
+    // product, one for each K-group count (1, 2, 4: index count / 2) that decode
+    // batches up to max_batch use
+    bf16_t *packed[4][3] = {};
 };
 
 // Training state of an instance created with iefwd_train_create: the flat
@@ -340,9 +340,11 @@ void run_forward(iefwd_instance *I, const float *x, int decode_pos = -1) {
     auto gemm = [&](Epi epi, const bf16_t *a, const LayerWeights &w, int j, const bf16_t *bias, const float *resid,
                     void *out, int N, int K, const QkvDst *qkv, const LnResid *ln_resid, const LnIn *ln_in = nullptr) {
         const bf16_t *wt = j == 0 ? w.wqkv : j == 1 ? w.wo : j == 2 ? w.w1 : w.w2;
-        if (skinny && !ln_resid)
-            return launch_gemm_skinny(epi, a, wt, bias, resid, out, T, N, K, qkv, s, ln_in, w.packed[j],
-                                      w.packed_groups[j]);
+        if (skinny && !ln_resid) {
+            const int groups = skinny_groups(T, N, K, ln_in != nullptr);
+            return launch_gemm_skinny(epi, a, wt, bias, resid, out, T, N, K, qkv, s, ln_in, w.packed[j][groups / 2],
+                                      groups);
+        }
         return launch_gemm(epi, a, wt, bias, resid, out, T, N, K, qkv, s, ln_resid, nullptr, n_cu);
     };
     auto attention_block = [&](int l, const bf16_t *y_bf16, const LayerWeights &w, const float *resid,
@@ -524,23 +526,29 @@ void upload_weights(iefwd_instance *I) {
     }
 }
 
-// Decode instances: the packed copy of each layer's four matrices, for the
-// K-group count a decode step of up to 4 sequences uses (with the pre-LN
-// LayerNorm fused into the QKV and FFN-up products).  Larger decode batches of
-// matrices whose group count differs read the row-major weights.
+// Decode instances: packed copies of each layer's four matrices, one for every
+// K-group count that a decode step of 1 .. max_batch (at most 16) sequences
+// uses (with the pre-LN LayerNorm fused into the QKV and FFN-up products where
+// it fits).  From row-major weights the four products of a step of 16 sequences
+// and width 1024 took 30 us a layer, from the copies 26.
 void pack_decode_weights(iefwd_instance *I) {
     const iefwd_config &c = I->cfg;
     const int d = (int)c.d_model, F = (int)c.d_ff;
-    const bool ln = skinny_ln_fits(1, d);
     const int shape[4][2] = {{3 * d, d}, {d, d}, {F, d}, {d, F}};
-    const bool fused[4] = {ln, false, ln, false};
+    bool used[4][3] = {};
+    for (int M = 1; M <= (int)std::min<uint32_t>(c.max_batch, 16); ++M) {
+        const bool ln = skinny_ln_fits(M, d);
+        for (int j = 0; j < 4; ++j) used[j][skinny_groups(M, shape[j][0], shape[j][1], ln && j % 2 == 0) / 2] = true;
+    }
     size_t bytes = 0;
     std::vector<size_t> offs;
     for (uint32_t l = 0; l < c.n_layers; ++l)
-        for (int j = 0; j < 4; ++j) {
-            offs.push_back(bytes);
-            bytes = round_up(bytes + (size_t)shape[j][0] * shape[j][1] * 2, 256);
-        }
+        for (int j = 0; j < 4; ++j)
+            for (int g = 0; g < 3; ++g) {
+                if (!used[j][g]) continue;
+                offs.push_back(bytes);
+                bytes = round_up(bytes + (size_t)shape[j][0] * shape[j][1] * 2, 256);
+            }
     if (hipMalloc(&I->pblob, bytes) != hipSuccess) {
         (void)hipGetLastError();
         I->pblob = nullptr;
@@ -551,14 +559,14 @@ void pack_decode_weights(iefwd_instance *I) {
     for (uint32_t l = 0; l < c.n_layers; ++l) {
         LayerWeights &w = I->layers[l];
         const bf16_t *src[4] = {w.wqkv, w.wo, w.w1, w.w2};
-        for (int j = 0; j < 4; ++j) {
-            const int N = shape[j][0], K = shape[j][1];
-            const int g = skinny_groups(1, N, K, fused[j]);
-            bf16_t *dst = reinterpret_cast<bf16_t *>(base + offs[oi++]);
-            hip_check(launch_skinny_pack(src[j], dst, N, K, g, I->stream), "weight packing");
-            w.packed[j] = dst;
-            w.packed_groups[j] = g;
-        }
+        for (int j = 0; j < 4; ++j)
+            for (int g = 0; g < 3; ++g) {
+                if (!used[j][g]) continue;
+                bf16_t *dst = reinterpret_cast<bf16_t *>(base + offs[oi++]);
+                hip_check(launch_skinny_pack(src[j], dst, shape[j][0], shape[j][1], 1 << g, I->stream),
+                          "weight packing");
+                w.packed[j][g] = dst;
+            }
     }
     hip_check(hipStreamSynchronize(I->stream), "hipStreamSynchronize");
 }

@@ -1,0 +1,65 @@
+"""The decode product's forms for 9-16 rows (two rows a wave in the LayerNorm
+prologue, 16 waves for narrow long-K products) and the packed copies an instance
+keeps for each class of decode batches (1-4, 5-8, 9-16 sequences)."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2503_05130_amd as ie
+import workloads as W
+from oracle import forward as F
+from tests.gpu_util import DEV, bf16_round, compare, f64, instance_config, sync, to_dev
+from tests.test_gpu_kernels import UBF, gemm_bound
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("M,N,K,ln", [
+    (9, 48, 128, True), (16, 3072, 1024, True), (13, 4096, 1024, True), (9, 384, 1792, True),
+    (9, 16, 2048, False), (16, 1024, 4096, False), (12, 2048, 2080, False),   # 16 waves
+    (16, 2064, 2048, False), (16, 1024, 2016, False),                         # 8 waves: too wide, too short
+])
+def test_nine_to_sixteen_rows(M, N, K, ln):
+    print(f"skinny M={M} N={N} K={K} ln={ln}", flush=True)
+    rng = np.random.default_rng(M + N + K)
+    w = bf16_round(rng.standard_normal((K, N)) * 0.05)
+    b = bf16_round(rng.standard_normal(N) * 0.1)
+    w_d, b_d = to_dev(w.t()), to_dev(b)
+    if ln:
+        z = (rng.standard_normal((M, K)) * 2 + 0.5).astype(np.float32)
+        g = (1 + 0.1 * rng.standard_normal(K)).astype(np.float32)
+        be = (0.1 * rng.standard_normal(K)).astype(np.float32)
+        lnarg, a_d = tuple(torch.from_numpy(t).to(DEV) for t in (z, g, be)) + (1e-5,), None
+        y = F.layer_norm(z.astype(np.float64), g.astype(np.float64), be.astype(np.float64), 1e-5)
+        extra = UBF * (np.abs(y) @ np.abs(f64(w)))   # the normalised rows are rounded to bf16
+    else:
+        a = bf16_round(rng.standard_normal((M, K)))
+        lnarg, a_d, y, extra = None, to_dev(a), f64(a), 0.0
+    out = torch.full((M, N), float("nan"), dtype=torch.bfloat16, device=DEV)
+    ie.test_gemm_skinny(ie.EPI_BIAS_BF16, a_d, w_d, b_d, None, out, M, N, K, ln=lnarg)
+    packed = torch.empty(N * K, dtype=torch.bfloat16, device=DEV)
+    groups = ie.test_skinny_groups(M, N, K, ln)
+    ie.test_skinny_pack(w_d, packed, N, K, groups)
+    out2 = torch.full_like(out, float("nan"))
+    ie.test_gemm_skinny_packed(ie.EPI_BIAS_BF16, a_d, packed, groups, b_d, None, out2, M, N, K, ln=lnarg)
+    sync()
+    ref = F.linear(y, f64(w), f64(b))
+    tol = gemm_bound(y, f64(w), K) + extra + UBF * 1.01 * np.abs(ref) + 1e-6
+    assert np.all(np.abs(f64(out) - ref) <= tol)
+    assert torch.equal(out.view(torch.int16), out2.view(torch.int16))
+
+
+@pytest.mark.parametrize("batch", [3, 6, 16])
+def test_instance_decodes_each_class(batch):
+    shape = W.model_shape("decoder_l24_d1024_s512", n_layers=2, n_out=0, b_std=0.02, ln_std=0.02, qk_std=0.05)
+    S = 20
+    x = W.make_input(9100 + batch, batch, S + 2, 1024)
+    print(f"decode class of {batch} sequences", flush=True)
+    with ie.Instance(**dict(instance_config(shape, 16, S + 2), kv_cache=1)) as inst:
+        inst.submit(np.ascontiguousarray(x[:, :S]))
+        inst.wait()
+        for i in range(2):
+            inst.decode(np.ascontiguousarray(x[:, S + i]), S + i)
+            got = inst.read_logits()[:, 0]
+            ma, rl = compare(got, F.forward(x[:, :S + i + 1], shape)[:, -1])
+            assert rl <= 1e-2 and ma <= 5e-2, (i, ma, rl)
