@@ -1,5 +1,6 @@
 // Fused softmax attention for gfx950: ctx = softmax(Q K^T / sqrt(dh) [+ causal]) V
-// per (batch, head), with an online softmax over 64-key chunks.
+// per (batch, head), with an online softmax over 64-key chunks (32-key blocks
+// up to 128 positions).
 //
 // Work split.  A workgroup of 4 waves owns 128 queries of one (batch, head);
 // each wave owns 32 of them.  Keys are streamed in 64-key chunks: the whole
@@ -31,8 +32,8 @@
 // exponent's fma, no rescale where no maximum rose, lane exchanges without
 // LDS, and V^T chunks stored in the fragments' key order.  Measured, before ->
 // after with the placement below: causal 16 heads x 4001 positions 100 -> 66 us,
-// 8 x 16 heads x 512 19.5 -> 14.2, 2 x 16 heads x 1024 of dim 128 34.7 -> 28.9;
-// 32 x 12 heads x 128 bidirectional 8.1 -> 7.7.  Not kept: a second group of
+// 8 x 16 heads x 512 19.5 -> 14.2, 2 x 16 heads x 1024 of dim 128 34.7 -> 28.9.
+// Not kept: a second group of
 // waves in the workgroup taking every other chunk (128 registers a lane, 14 of
 // them spilled: 8 x 16 x 512 19.6 us).
 //
@@ -73,6 +74,13 @@ __device__ inline float half_sum(float v) {
     return __uint_as_float(r[0]) + __uint_as_float(r[1]);
 }
 
+// x * scale rounded on its own, whatever follows.
+__device__ inline float scaled(float x, float scale) {
+    float y = x * scale;
+    asm volatile("" : "+v"(y));
+    return y;
+}
+
 __device__ inline bf16x8 as_bf16x8(u32x4 v) { return __builtin_bit_cast(bf16x8, v); }
 
 // Workgroup i of the grid -> (query group, batch * head); false for a padding
@@ -100,7 +108,7 @@ __device__ inline bool place(int i, int n_bh, int n_groups, int &group, int &bh)
     return bh < n_bh;
 }
 
-template <int DH, bool CAUSAL>
+template <int DH, bool CAUSAL, bool SHORT>
 __global__ __launch_bounds__(kThreads) void attention_kernel(
     const bf16_t *__restrict__ Q, const bf16_t *__restrict__ K, const bf16_t *__restrict__ Vt,
     bf16_t *__restrict__ ctx, int n_bh, int n_groups, int n_heads, int seq, int k_rows, int seq_pad,
@@ -202,11 +210,11 @@ __global__ __launch_bounds__(kThreads) void attention_kernel(
         if (c + 1 < n_chunks) gload(c + 1);
         const bf16_t *kb = lds + buf * (K_ELEMS + V_ELEMS);
         const bf16_t *vb = kb + K_ELEMS;
-        // NB 32-key blocks of the chunk at once (2, or 1 where only the first is
-        // visible): one maximum, one rescale and the blocks' products side by side
-        auto blocks = [&](auto nb) {
+        // NB 32-key blocks of the chunk from block b0 on at once: their products side
+        // by side, one maximum, one rescale
+        auto blocks = [&](auto nb, int b0) {
             constexpr int NB = decltype(nb)::value;
-            const int k0 = c * kChunk;
+            const int k0 = c * kChunk + 32 * b0;
             // ---- S^T blocks (32 keys x 32 queries)
             f32x16 st[NB];
 #pragma unroll
@@ -218,7 +226,7 @@ __global__ __launch_bounds__(kThreads) void attention_kernel(
 #pragma unroll
                 for (int sb = 0; sb < NB; ++sb) {
                     const bf16x8 kf = as_bf16x8(*reinterpret_cast<const u32x4 *>(
-                        kb + (sb * 32 + col) * K_STRIDE + ks * 16 + half * 8));
+                        kb + ((b0 + sb) * 32 + col) * K_STRIDE + ks * 16 + half * 8));
                     st[sb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf, qf[ks], st[sb], 0, 0, 0);
                 }
             // key of accumulator entry r: k0 + 32 sb + 8 (r / 4) + 4 half + r % 4.  Only the
@@ -233,17 +241,22 @@ __global__ __launch_bounds__(kThreads) void attention_kernel(
                         if (key >= seq || (CAUSAL && key > query)) st[sb][r] = -INFINITY;
                     }
             }
+            if constexpr (SHORT) {
+#pragma unroll
+                for (int r = 0; r < 16; ++r) st[0][r] = scaled(st[0][r], scale_log2e);
+            }
             float mx = st[0][0];
 #pragma unroll
             for (int sb = 0; sb < NB; ++sb)
 #pragma unroll
                 for (int r = 0; r < 16; ++r) mx = fmaxf(mx, st[sb][r]);
-            mx = half_max(mx) * scale_log2e;
+            mx = half_max(mx);
+            if constexpr (!SHORT) mx *= scale_log2e;
             const float m_new = fmaxf(m_run, mx);   // finite: key 0 is visible to every query
+            float alpha = 1.f;
             // blocks that raise no query's maximum rescale nothing (times 1)
             if (__any(m_new > m_run)) {
-                const float alpha = __builtin_amdgcn_exp2f(m_run - m_new);
-                l_run *= alpha;
+                alpha = __builtin_amdgcn_exp2f(m_run - m_new);
                 m_run = m_new;
 #pragma unroll
                 for (int d = 0; d < DB; ++d)
@@ -255,28 +268,34 @@ __global__ __launch_bounds__(kThreads) void attention_kernel(
             for (int sb = 0; sb < NB; ++sb)
 #pragma unroll
                 for (int r = 0; r < 16; ++r) {
-                    st[sb][r] = __builtin_amdgcn_exp2f(__builtin_fmaf(st[sb][r], scale_log2e, -m_run));
-                    psum[r & 1] += st[sb][r];
+                    st[sb][r] = __builtin_amdgcn_exp2f(SHORT ? st[sb][r] - m_run
+                                                             : __builtin_fmaf(st[sb][r], scale_log2e, -m_run));
+                    psum[SHORT ? 0 : r & 1] += st[sb][r];
                 }
-            l_run += psum[0] + psum[1];
+            l_run = __builtin_fmaf(l_run, alpha, SHORT ? psum[0] : psum[0] + psum[1]);
             // ---- ctx^T += V^T P^T, 16-key steps
 #pragma unroll
             for (int j = 0; j < 2 * NB; ++j) {
                 bf16x8 pf;   // P^T fragment: entries r = 8 (j % 2) .. + 7 of block j / 2
 #pragma unroll
                 for (int e = 0; e < 8; ++e) pf[e] = (__bf16)st[j / 2][8 * (j % 2) + e];
-                // chunk-local keys 16 j + 4 half + {0..3, 8..11}
+                // chunk-local keys 32 b0 + 16 j + 4 half + {0..3, 8..11}
 #pragma unroll
                 for (int d = 0; d < DB; ++d) {
                     const u32x4 v = *reinterpret_cast<const u32x4 *>(
-                        vb + (d * 32 + col) * kVtStride + 16 * j + 8 * half);
+                        vb + (d * 32 + col) * kVtStride + 32 * b0 + 16 * j + 8 * half);
                     acc[d] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(v), pf, acc[d], 0, 0, 0);
                 }
             }
         };
         const int left = wave_active ? wave_key_end - c * kChunk : 0;   // wave-uniform
-        if (left > 32) blocks(std::integral_constant<int, 2>{});
-        else if (left > 0) blocks(std::integral_constant<int, 1>{});
+        if constexpr (SHORT) {
+            if (left > 0) blocks(std::integral_constant<int, 1>{}, 0);
+            if (left > 32) blocks(std::integral_constant<int, 1>{}, 1);
+        } else {
+            if (left > 32) blocks(std::integral_constant<int, 2>{}, 0);
+            else if (left > 0) blocks(std::integral_constant<int, 1>{}, 0);
+        }
         if (c + 1 < n_chunks) lstore(buf ^ 1);
         __syncthreads();
     }
@@ -306,7 +325,13 @@ hipError_t launch(const bf16_t *q, const bf16_t *k, const bf16_t *vt, bf16_t *ct
     const int bh = batch * n_heads;
     const dim3 grid(kXcds * ((bh + kXcds - 1) / kXcds) * groups), block(kThreads);
     const float scale_log2e = 1.4426950408889634f / sqrtf((float)DH);
-    return launch_kernel(attention_kernel<DH, CAUSAL>, grid, block, s, q, k, vt, ctx, bh, groups, n_heads,
+    // Up to 128 positions (every training step) the sums keep their order: a
+    // maximum per 32 keys and scores scaled before it, the bits such sequences have
+    // always had.  A 64-key step would save them 0.4 us of 8.1 (32 x 12 heads).
+    if (seq <= 128)
+        return launch_kernel(attention_kernel<DH, CAUSAL, true>, grid, block, s, q, k, vt, ctx, bh, groups, n_heads,
+                             seq, k_rows, vt_stride, scale_log2e);
+    return launch_kernel(attention_kernel<DH, CAUSAL, false>, grid, block, s, q, k, vt, ctx, bh, groups, n_heads,
                          seq, k_rows, vt_stride, scale_log2e);
 }
 
