@@ -578,7 +578,8 @@ hipError_t launch_skinny(Epi epi, const GemmParams &p, hipStream_t stream) {
 #undef EPI
     case Epi::BiasLnResidF32:
     case Epi::F32:
-    case Epi::GeluBwdBf16: break;
+    case Epi::GeluBwdBf16:
+    case Epi::BiasGelu2Bf16: break;
     }
     return hipErrorInvalidValue;
 }
@@ -683,7 +684,8 @@ hipError_t launch_gemm_skinny(Epi epi, const bf16_t *a, const bf16_t *w, const b
                               void *out, int M, int N, int K, const QkvDst *qkv, hipStream_t stream,
                               const LnIn *ln_in, const bf16_t *w_packed, int packed_groups) {
     if (M <= 0) return hipSuccess;
-    if (M > 16 || N % 16 || K % 32 || epi == Epi::BiasLnResidF32 || epi == Epi::F32 || epi == Epi::GeluBwdBf16)
+    if (M > 16 || N % 16 || K % 32 || epi == Epi::BiasLnResidF32 || epi == Epi::F32 || epi == Epi::GeluBwdBf16 ||
+        epi == Epi::BiasGelu2Bf16)
         return hipErrorInvalidValue;
     if (ln_in && !skinny_ln_fits(M, K)) return hipErrorInvalidValue;
     GemmParams p{};

@@ -14,6 +14,7 @@ enum class Epi : int {
     BiasLnResidF32 = 4, // out f32  = LN(z) + acc + b, LN(z) rebuilt from z and its row stats
     F32 = 5,            // out f32  = acc                      (weight gradients)
     GeluBwdBf16 = 6,    // out bf16 = acc * GELU'(aux), aux bf16 [M, N] (the GELU's input)
+    BiasGelu2Bf16 = 7,  // out bf16 = acc + b, out2 bf16 = GELU(out) (training keeps both)
 };
 
 // Row statistics a LayerNorm kernel leaves for a later consumer: the residual
@@ -54,7 +55,18 @@ inline int attn_seq_pad(int seq) { return (seq + 63) / 64 * 64; }
 hipError_t launch_gemm(Epi epi, const bf16_t *a, const bf16_t *w, const bf16_t *bias,
                        const float *resid, void *out, int M, int N, int K,
                        const QkvDst *qkv, hipStream_t stream, const LnResid *ln = nullptr,
-                       const bf16_t *aux = nullptr, int n_cu = 256);
+                       const bf16_t *aux = nullptr, int n_cu = 256, bf16_t *out2 = nullptr);
+
+// Up to kMaxGemmGroup products out = A W^T of one contraction length K in one
+// launch, fp32 outputs (Epi::F32; a layer's weight gradients).  Each sums
+// exactly as launch_gemm(Epi::F32, ...) does.  M >= 1, N % 64 == 0, K % 64 == 0.
+struct GemmJob {
+    const bf16_t *a, *w;
+    float *out;
+    int M, N;
+};
+constexpr int kMaxGemmGroup = 4;
+hipError_t launch_gemm_group(const GemmJob *jobs, int n_jobs, int K, hipStream_t stream, int n_cu = 256);
 
 // How launch_gemm runs a product: the K summation order (a function of the
 // weight shape (N, K) alone), the order the chosen tile sums in, and the tile.

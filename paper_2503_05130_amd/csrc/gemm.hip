@@ -350,7 +350,8 @@ __device__ inline void main_loop(const GemmParams &p, bf16_t *lds, int wave, int
 // whole workgroup stores it in 16-byte row segments.  Written straight from
 // the MFMA layout, one store instruction would cover 16 rows x 32 bytes.
 constexpr bool staged(Epi e) {
-    return e == Epi::BiasBf16 || e == Epi::BiasGeluBf16 || e == Epi::Qkv || e == Epi::GeluBwdBf16;
+    return e == Epi::BiasBf16 || e == Epi::BiasGeluBf16 || e == Epi::Qkv || e == Epi::GeluBwdBf16 ||
+           e == Epi::BiasGelu2Bf16;
 }
 constexpr bool has_bias(Epi e) { return e != Epi::F32 && e != Epi::GeluBwdBf16; }
 
@@ -525,6 +526,13 @@ __device__ inline void store_tile(const GemmParams &p, const bf16_t *ctile, bool
             o = static_cast<bf16_t *>(p.out) + (size_t)t * p.N + f;
         }
         *reinterpret_cast<u32x4 *>(o) = v;
+        if constexpr (EPI == Epi::BiasGelu2Bf16) {   // GELU of the value as rounded
+            u32x4 g;
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                g[e] = pack2(gelu(__uint_as_float(v[e] << 16)), gelu(__uint_as_float(v[e] & 0xffff0000u)));
+            *reinterpret_cast<u32x4 *>(p.out2 + (size_t)t * p.N + f) = g;
+        }
     }
 }
 
@@ -537,14 +545,12 @@ constexpr int lds_elems() {
     return n;
 }
 
-// One output tile per workgroup.
+// One output tile: tile l of the product, by the whole workgroup.
 template <class C, Epi EPI>
-__global__ __launch_bounds__(C::NT) __attribute__((amdgpu_waves_per_eu(C::WPE))) void gemm_kernel(GemmParams p) {
+__device__ inline void run_tile(const GemmParams &p, int l, bf16_t *lds) {
     constexpr int FN = C::FN, FM = C::FM;
-    __shared__ __attribute__((aligned(1024))) bf16_t lds[lds_elems<C, EPI>()];
-    static_assert(lds_elems<C, EPI>() * 2 <= 163840, "LDS");
     int tm, tn;
-    grouped_tile(xcd_contiguous(blockIdx.x, gridDim.x), p.tiles_m, p.tiles_n, tm, tn);
+    grouped_tile(l, p.tiles_m, p.tiles_n, tm, tn);
     const int m0 = tm * C::BM, n0 = tn * C::BN;
     // the wave index is uniform across the wave: held in a scalar register, so
     // that every branch on it (tile, copy counts) is a scalar branch
@@ -573,6 +579,30 @@ __global__ __launch_bounds__(C::NT) __attribute__((amdgpu_waves_per_eu(C::WPE)))
         __syncthreads();
         store_tile<C, EPI>(p, lds, vt_tile, threadIdx.x, C::NT, m0, n0);
     }
+}
+
+template <class C, Epi EPI>
+__global__ __launch_bounds__(C::NT) __attribute__((amdgpu_waves_per_eu(C::WPE))) void gemm_kernel(GemmParams p) {
+    __shared__ __attribute__((aligned(1024))) bf16_t lds[lds_elems<C, EPI>()];
+    static_assert(lds_elems<C, EPI>() * 2 <= 163840, "LDS");
+    run_tile<C, EPI>(p, xcd_contiguous(blockIdx.x, gridDim.x), lds);
+}
+
+// Several products in one launch: tile l belongs to job j with first[j] <= l <
+// first[j + 1].
+struct GemmGroup {
+    GemmParams job[kMaxGemmGroup];
+    int32_t first[kMaxGemmGroup + 1];
+    int32_t n;
+};
+
+template <class C>
+__global__ __launch_bounds__(C::NT) __attribute__((amdgpu_waves_per_eu(C::WPE))) void gemm_group_kernel(GemmGroup g) {
+    __shared__ __attribute__((aligned(1024))) bf16_t lds[lds_elems<C, Epi::F32>()];
+    const int l = xcd_contiguous(blockIdx.x, gridDim.x);
+    int j = 0;
+    while (j + 1 < g.n && l >= g.first[j + 1]) ++j;
+    run_tile<C, Epi::F32>(g.job[j], l - g.first[j], lds);
 }
 
 // Tile configurations.
@@ -655,16 +685,25 @@ long ceil_div(long a, long b) { return (a + b - 1) / b; }
 //    64 x 64 tiles do: 4096 x 2368 x 768, 27 against 32 us).
 // Every tile shape of an order adds the same terms in the same sequence, so
 // the choice may follow the launch (M and n_cu) without changing a bit.
-const TileInfo &choose_tile(int M, int N, int K, int align, int n_cu, bool wide_ok = true) {
-    const bool split = split_k_order(N, K);
+struct Shape {
+    int M, N, align;
+};
+
+const TileInfo &choose_tile(const Shape *shapes, int n_shapes, int K, int n_cu, bool wide_ok = true) {
+    const bool split = split_k_order(0, K);
     const TileInfo *best = nullptr;
     long best_cost = 0;
     for (const TileInfo &t : kTiles) {
-        if (t.split != split || align % t.bn) continue;
+        if (t.split != split) continue;
         if (t.tile == Tile::S128x192 && !wide_ok) continue;
         if (t.tile == Tile::S256x256 && K < 1024) continue;
-        const long n = ceil_div(M, t.bm) * (N / t.bn);
-        if (t.tile == Tile::S128x64 && n > n_cu) continue;
+        long n = 0;
+        bool divides = true;
+        for (int i = 0; i < n_shapes; ++i) {
+            divides = divides && shapes[i].align % t.bn == 0;
+            n += ceil_div(shapes[i].M, t.bm) * (shapes[i].N / t.bn);
+        }
+        if (!divides || (t.tile == Tile::S128x64 && n > n_cu)) continue;
         const long cost = ceil_div(n, n_cu) * (K / 64) * t.step +
                           ceil_div(n, (long)n_cu * t.per_cu) * (split ? kRoundSplit : kRoundSequential);
         if (!best || cost < best_cost) {
@@ -673,6 +712,11 @@ const TileInfo &choose_tile(int M, int N, int K, int align, int n_cu, bool wide_
         }
     }
     return *best;   // 64 x 64 divides every width
+}
+
+const TileInfo &choose_tile(int M, int N, int K, int align, int n_cu, bool wide_ok = true) {
+    const Shape s{M, N, align};
+    return choose_tile(&s, 1, K, n_cu, wide_ok);
 }
 
 template <class C>
@@ -690,8 +734,23 @@ hipError_t launch_tile(Epi epi, GemmParams &p, hipStream_t s) {
         else return launch_kernel(gemm_kernel<C, Epi::BiasLnResidF32>, grid, block, s, p);
     case Epi::F32: return launch_kernel(gemm_kernel<C, Epi::F32>, grid, block, s, p);
     case Epi::GeluBwdBf16: return launch_kernel(gemm_kernel<C, Epi::GeluBwdBf16>, grid, block, s, p);
+    case Epi::BiasGelu2Bf16: return launch_kernel(gemm_kernel<C, Epi::BiasGelu2Bf16>, grid, block, s, p);
     }
     return hipErrorInvalidValue;
+}
+
+template <class C>
+hipError_t launch_group(GemmGroup &g, hipStream_t s) {
+    int tiles = 0;
+    for (int j = 0; j < g.n; ++j) {
+        GemmParams &p = g.job[j];
+        p.tiles_m = (p.M + C::BM - 1) / C::BM;
+        p.tiles_n = p.N / C::BN;
+        g.first[j] = tiles;
+        tiles += p.tiles_m * p.tiles_n;
+    }
+    g.first[g.n] = tiles;
+    return launch_kernel(gemm_group_kernel<C>, dim3(tiles), dim3(C::NT), s, g);
 }
 
 }  // namespace
@@ -703,23 +762,50 @@ GemmPlan gemm_plan(int M, int N, int K, int align, int n_cu, bool ln_residual) {
 
 hipError_t launch_gemm(Epi epi, const bf16_t *a, const bf16_t *w, const bf16_t *bias,
                        const float *resid, void *out, int M, int N, int K, const QkvDst *qkv,
-                       hipStream_t stream, const LnResid *ln, const bf16_t *aux, int n_cu) {
+                       hipStream_t stream, const LnResid *ln, const bf16_t *aux, int n_cu, bf16_t *out2) {
     if (M <= 0) return hipSuccess;
     if (N % 64 || K % 64 || N <= 0 || K <= 0) return hipErrorInvalidValue;
-    if (epi == Epi::GeluBwdBf16 && !aux) return hipErrorInvalidValue;
+    if ((epi == Epi::GeluBwdBf16 && !aux) || (epi == Epi::BiasGelu2Bf16 && !out2)) return hipErrorInvalidValue;
     GemmParams p{};
-    p.a = a; p.w = w; p.bias = bias; p.resid = resid; p.out = out; p.aux = aux;
+    p.a = a; p.w = w; p.bias = bias; p.resid = resid; p.out = out; p.aux = aux; p.out2 = out2;
     p.M = M; p.N = N; p.K = K;
     if (qkv) p.qkv = *qkv;
     if (ln) p.ln = *ln;
     // N is a multiple of 64 (checked by the callers); d_model a multiple of 128
     const int align = epi == Epi::Qkv ? p.qkv.d_model : N;
     switch (choose_tile(M, N, K, align, n_cu, epi != Epi::BiasLnResidF32).tile) {
-#define TILE(T) case Tile::T: return launch_tile<T>(epi, p, stream);
-    TILE(S32x32) TILE(S32x64) TILE(S64x64) TILE(S64x96) TILE(S128x64) TILE(S128x96) TILE(S128x96p) TILE(S128x128)
-    TILE(S128x192) TILE(S256x256) TILE(E32x32) TILE(E32x64) TILE(E64x64) TILE(E64x96) TILE(E128x64) TILE(E2x64x96)
-    TILE(E128x128) TILE(E256x128)
-#undef TILE
+#define IEFWD_TILES(X) \
+    X(S32x32) X(S32x64) X(S64x64) X(S64x96) X(S128x64) X(S128x96) X(S128x96p) X(S128x128) X(S128x192) X(S256x256) \
+    X(E32x32) X(E32x64) X(E64x64) X(E64x96) X(E128x64) X(E2x64x96) X(E128x128) X(E256x128)
+#define X(T) case Tile::T: return launch_tile<T>(epi, p, stream);
+        IEFWD_TILES(X)
+#undef X
+    }
+    return hipErrorInvalidValue;
+}
+
+// The tile is chosen for the jobs' tiles together: products too small to fill
+// the chip each with the tile that reuses its operands most do so together.
+// (Width 768, 4096 tokens, the four weight gradients of a layer: 91 us in four
+// launches of 128 x 96, 128 x 64 and 64 x 64 tiles, 68 us in one of 216 tiles of
+// 256 x 128.)
+hipError_t launch_gemm_group(const GemmJob *jobs, int n_jobs, int K, hipStream_t stream, int n_cu) {
+    if (n_jobs <= 0) return hipSuccess;
+    if (n_jobs > kMaxGemmGroup || K <= 0 || K % 64) return hipErrorInvalidValue;
+    GemmGroup g{};
+    g.n = n_jobs;
+    Shape shapes[kMaxGemmGroup];
+    for (int j = 0; j < n_jobs; ++j) {
+        if (jobs[j].M < 1 || jobs[j].N <= 0 || jobs[j].N % 64) return hipErrorInvalidValue;
+        GemmParams &p = g.job[j];
+        p.a = jobs[j].a; p.w = jobs[j].w; p.out = jobs[j].out;
+        p.M = jobs[j].M; p.N = jobs[j].N; p.K = K;
+        shapes[j] = {p.M, p.N, p.N};
+    }
+    switch (choose_tile(shapes, n_jobs, K, n_cu).tile) {
+#define X(T) case Tile::T: return launch_group<T>(g, stream);
+        IEFWD_TILES(X)
+#undef X
     }
     return hipErrorInvalidValue;
 }

@@ -28,6 +28,7 @@ struct GemmParams {
     LnResid ln;
     LnIn lnin;
     const bf16_t *aux;   // Epi::GeluBwdBf16: the GELU's input [M, N]
+    bf16_t *out2;        // Epi::BiasGelu2Bf16: GELU(out) [M, N]
 };
 
 __device__ inline bf16_t f32_to_bf16(float f) {

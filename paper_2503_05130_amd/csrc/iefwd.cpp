@@ -174,7 +174,9 @@ struct TrainState {
     // backward scratch
     float *dxa = nullptr, *dxb = nullptr, *dz = nullptr, *xl = nullptr, *loss_t = nullptr, *dlogits = nullptr;
     float *colpart = nullptr, *loss_sum = nullptr;   // column-sum partials of one layer; the loss
-    bf16_t *dzb = nullptr, *dvb = nullptr, *dctx = nullptr, *dqkv = nullptr, *ta = nullptr, *tb = nullptr;
+    bf16_t *dzb = nullptr, *dzb1 = nullptr, *dvb = nullptr, *dctx = nullptr, *dqkv = nullptr;
+    // transposed operands of a layer's weight gradients: dz2, u, dv, X1, dz1, ctx, dqkv, X
+    bf16_t *tr[8] = {};
     bf16_t *zero_bias = nullptr, *attn_scratch = nullptr;
     int32_t *labels = nullptr;
 
@@ -738,7 +740,10 @@ void train_alloc(iefwd_instance *I, const iefwd_train_params &hp) {
     const size_t o_colpart = reserve((size_t)colpart_rows((int)T, (int)d) * std::max(9 * d + F, no * d + no + 1) * 4);
     const size_t o_lsum = reserve(4);
     const size_t o_dzb = reserve(T * d * 2), o_dvb = reserve(T * F * 2), o_dctx = reserve(T * d * 2);
-    const size_t o_dqkv = reserve(T * 3 * d * 2), o_ta = reserve(wide * T * 2), o_tb = reserve(wide * T * 2);
+    const size_t o_dqkv = reserve(T * 3 * d * 2), o_dzb1 = reserve(T * d * 2);
+    const size_t tr_width[8] = {d, F, F, d, d, d, 3 * d, d};
+    size_t o_tr[8];
+    for (int i = 0; i < 8; ++i) o_tr[i] = reserve(tr_width[i] * T * 2);
     const size_t o_zero = reserve(wide * 2), o_lab = reserve(T * 4);
     const size_t o_ascr = reserve(attention_backward_scratch((int)c.max_batch, (int)c.n_heads) * 2);
     if (hipMalloc(&t.blob, bytes) != hipSuccess) {
@@ -768,8 +773,9 @@ void train_alloc(iefwd_instance *I, const iefwd_train_params &hp) {
     }
     t.dxa = f32(o_dxa); t.dxb = f32(o_dxb); t.dz = f32(o_dz); t.xl = f32(o_xl); t.loss_t = f32(o_loss);
     t.dlogits = f32(o_dl); t.colpart = f32(o_colpart); t.loss_sum = f32(o_lsum);
-    t.dzb = b16(o_dzb); t.dvb = b16(o_dvb); t.dctx = b16(o_dctx); t.dqkv = b16(o_dqkv); t.ta = b16(o_ta);
-    t.tb = b16(o_tb); t.zero_bias = b16(o_zero); t.attn_scratch = b16(o_ascr);
+    t.dzb = b16(o_dzb); t.dvb = b16(o_dvb); t.dctx = b16(o_dctx); t.dqkv = b16(o_dqkv); t.dzb1 = b16(o_dzb1);
+    for (int i = 0; i < 8; ++i) t.tr[i] = b16(o_tr[i]);
+    t.zero_bias = b16(o_zero); t.attn_scratch = b16(o_ascr);
     t.labels = reinterpret_cast<int32_t *>(b + o_lab);
 
     // segments: where each tensor's updated value goes (the forward's copy)
@@ -886,9 +892,8 @@ void train_run(iefwd_instance *I, const float *x) {
         fwd(IEFWD_K_LN, "layernorm",
             [&] { return launch_layernorm(sv.z1, w.g1, w.be1, nullptr, sv.h1b, T, d, eps, s, sv.st1); });
         fwd(IEFWD_K_FFN1, "ffn1 gemm",
-            [&] { return launch_gemm(Epi::BiasBf16, sv.h1b, w.w1, w.b1, nullptr, sv.v, T, F, d, nullptr, s,
-                                     nullptr, nullptr, n_cu); });
-        fwd(IEFWD_K_FFN1, "gelu", [&] { return launch_gelu(sv.v, sv.u, (size_t)T * F, s); });
+            [&] { return launch_gemm(Epi::BiasGelu2Bf16, sv.h1b, w.w1, w.b1, nullptr, sv.v, T, F, d, nullptr, s,
+                                     nullptr, nullptr, n_cu, sv.u); });
         const LnResid r1{sv.z1, sv.st1, w.g1, w.be1};
         fwd(IEFWD_K_FFN2, "ffn2 gemm", [&] {
             return launch_gemm(Epi::BiasLnResidF32, sv.u, w.w2, w.b2, nullptr, sv.z2, T, d, F, nullptr, s,
@@ -916,10 +921,10 @@ void train_run(iefwd_instance *I, const float *x) {
 
     // ---- backward, last layer first; dxa holds dL/d(layer output)
     // LayerNorm backward (dz fp32 and bf16) with its parameters' partial sums
-    auto ln_backward = [&](const float *dy, const float *z, const float *st, const float *gamma, size_t off_g,
-                           size_t off_b, int col) {
+    auto ln_backward = [&](const float *dy, const float *z, const float *st, const float *gamma, bf16_t *dzb,
+                           size_t off_g, size_t off_b, int col) {
         bwd("layernorm backward", [&] {
-            return launch_ln_backward_params(dy, z, st, gamma, t.dz, t.dzb, region(col), region(col + d), T, d, s);
+            return launch_ln_backward_params(dy, z, st, gamma, t.dz, dzb, region(col), region(col + d), T, d, s);
         });
         finals.push_back({region(col), t.grad + off_g, ln_parts, d});
         finals.push_back({region(col + d), t.grad + off_b, ln_parts, d});
@@ -932,40 +937,22 @@ void train_run(iefwd_instance *I, const float *x) {
         const TrainState::Transposed &wt = t.wt[l];
         const auto &o = t.off[l];
         // LN2: dz2 (fp32 in dz, bf16 in dzb)
-        ln_backward(t.dxa, sv.z2, sv.st2, w.g2, o[10], o[11], c_ln2);
-        // FFN-down: dW2 = dz2^T u, db2, dv = (dz2 W2) GELU'(v)
-        transposes({{t.dzb, t.ta, T, d, region(c_b2)}, {sv.u, t.tb, T, F}});
-        finals.push_back({region(c_b2), t.grad + o[9], blocks64, d});
-        bwd_gemm("dW2 gemm", [&] {
-            return launch_gemm(Epi::F32, t.ta, t.tb, nullptr, nullptr, t.grad + o[8], d, F, T, nullptr, s,
-                               nullptr, nullptr, n_cu);
-        });
+        ln_backward(t.dxa, sv.z2, sv.st2, w.g2, t.dzb, o[10], o[11], c_ln2);
+        // FFN-down: dv = (dz2 W2) GELU'(v)
         bwd_gemm("dv gemm", [&] {
             return launch_gemm(Epi::GeluBwdBf16, t.dzb, wt.w2, nullptr, nullptr, t.dvb, T, F, d, nullptr, s, nullptr,
                                sv.v, n_cu);
         });
-        // FFN-up: dW1 = dv^T X1, db1, dX1 = dz2 + dv W1
-        transposes({{t.dvb, t.ta, T, F, region(c_b1)}, {sv.h1b, t.tb, T, d}});
-        finals.push_back({region(c_b1), t.grad + o[7], blocks64, F});
-        bwd_gemm("dW1 gemm", [&] {
-            return launch_gemm(Epi::F32, t.ta, t.tb, nullptr, nullptr, t.grad + o[6], F, d, T, nullptr, s,
-                               nullptr, nullptr, n_cu);
-        });
+        // FFN-up: dX1 = dz2 + dv W1
         bwd_gemm("dX1 gemm", [&] {
             return launch_gemm(Epi::BiasResidF32, t.dvb, wt.w1, t.zero_bias, t.dz, t.dxb, T, d, F, nullptr, s,
                                nullptr, nullptr, n_cu);
         });
-        // LN1: dz1
-        ln_backward(t.dxb, sv.z1, sv.st1, w.g1, o[4], o[5], c_ln1);
-        // out-projection: dWo = dz1^T ctx, dbo, dctx = dz1 Wo
-        transposes({{t.dzb, t.ta, T, d, region(c_bo)}, {sv.ctx, t.tb, T, d}});
-        finals.push_back({region(c_bo), t.grad + o[3], blocks64, d});
-        bwd_gemm("dWo gemm", [&] {
-            return launch_gemm(Epi::F32, t.ta, t.tb, nullptr, nullptr, t.grad + o[2], d, d, T, nullptr, s,
-                               nullptr, nullptr, n_cu);
-        });
+        // LN1: dz1 (fp32 in dz, bf16 in dzb1)
+        ln_backward(t.dxb, sv.z1, sv.st1, w.g1, t.dzb1, o[4], o[5], c_ln1);
+        // out-projection: dctx = dz1 Wo
         bwd_gemm("dctx gemm", [&] {
-            return launch_gemm(Epi::BiasBf16, t.dzb, wt.wo, t.zero_bias, nullptr, t.dctx, T, d, d, nullptr, s,
+            return launch_gemm(Epi::BiasBf16, t.dzb1, wt.wo, t.zero_bias, nullptr, t.dctx, T, d, d, nullptr, s,
                                nullptr, nullptr, n_cu);
         });
         // attention
@@ -973,18 +960,27 @@ void train_run(iefwd_instance *I, const float *x) {
             return launch_attention_backward(sv.q, sv.k, sv.vt, sv.ctx, t.dctx, t.dqkv, t.attn_scratch, B, H, S, dh,
                                              spad, causal, s);
         });
-        // QKV: dWqkv = dqkv^T X, dbqkv, dX = dz1 + dqkv Wqkv
-        transposes({{t.dqkv, t.ta, T, 3 * d, region(c_bqkv)}, {sv.hb, t.tb, T, d}});
-        finals.push_back({region(c_bqkv), t.grad + o[1], blocks64, 3 * d});
-        bwd_gemm("dWqkv gemm", [&] {
-            return launch_gemm(Epi::F32, t.ta, t.tb, nullptr, nullptr, t.grad + o[0], 3 * d, d, T, nullptr, s,
-                               nullptr, nullptr, n_cu);
-        });
+        // QKV: dX = dz1 + dqkv Wqkv
         if (l > 0)
             bwd_gemm("dX gemm", [&] {
                 return launch_gemm(Epi::BiasResidF32, t.dqkv, wt.wqkv, t.zero_bias, t.dz, t.dxa, T, d, 3 * d, nullptr,
                                    s, nullptr, nullptr, n_cu);
             });
+        // weight gradients of the layer, dW = dC^T A: all eight operands transposed in one launch (with the
+        // bias gradients' first stages), the four products in another
+        transposes({{t.dzb, t.tr[0], T, d, region(c_b2)}, {sv.u, t.tr[1], T, F},
+                    {t.dvb, t.tr[2], T, F, region(c_b1)}, {sv.h1b, t.tr[3], T, d},
+                    {t.dzb1, t.tr[4], T, d, region(c_bo)}, {sv.ctx, t.tr[5], T, d},
+                    {t.dqkv, t.tr[6], T, 3 * d, region(c_bqkv)}, {sv.hb, t.tr[7], T, d}});
+        finals.push_back({region(c_b2), t.grad + o[9], blocks64, d});
+        finals.push_back({region(c_b1), t.grad + o[7], blocks64, F});
+        finals.push_back({region(c_bo), t.grad + o[3], blocks64, d});
+        finals.push_back({region(c_bqkv), t.grad + o[1], blocks64, 3 * d});
+        bwd_gemm("weight gradients", [&] {
+            const GemmJob jobs[4] = {{t.tr[0], t.tr[1], t.grad + o[8], d, F}, {t.tr[2], t.tr[3], t.grad + o[6], F, d},
+                                     {t.tr[4], t.tr[5], t.grad + o[2], d, d}, {t.tr[6], t.tr[7], t.grad + o[0], 3 * d, d}};
+            return launch_gemm_group(jobs, 4, T, s, n_cu);
+        });
         flush_finals();
     }
 

@@ -43,8 +43,6 @@ struct TransposeJob {
 };
 constexpr int kMaxTransposeJobs = 48;
 hipError_t launch_transposes(const TransposeJob *jobs, int n_jobs, hipStream_t stream);
-// u = GELU(v) elementwise, bf16; n % 8 == 0.
-hipError_t launch_gelu(const bf16_t *v, bf16_t *u, size_t n, hipStream_t stream);
 // LayerNorm backward per row: dz = rstd (g - mean(g) - x^ mean(g x^)), g = dy gamma,
 // x^ = (z - mean) rstd with the forward's {mean, rstd}.  dz (fp32, may be null)
 // and dzb (bf16) [rows, d]; d % 4 == 0.

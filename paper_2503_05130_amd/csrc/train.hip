@@ -9,7 +9,6 @@
 //                      (the bias gradients' first stage)
 //   colsum             per row block: column sums (fp32 or bf16 input), fixed
 //                      order; the last stages of several sums in one launch
-//   gelu               u = GELU(v), bf16 -> bf16
 //   ln_backward        dz = rstd (g - mean(g) - x^ mean(g x^)), g = dy gamma,
 //                      one wave per row, fp32; writes fp32 and bf16
 //   ln_param_partials  per 256-row chunk: sum dy x^ and sum dy per column
@@ -24,7 +23,6 @@
 //   adamw              one pass over every parameter (fp32 master, moments),
 //                      writing the forward's bf16 (or fp32) copy
 // Every reduction runs in a fixed order, so a training step is deterministic.
-#include "gelu.h"
 #include "kernels.h"
 
 namespace iefwd {
@@ -114,21 +112,6 @@ __global__ __launch_bounds__(256) void transpose_jobs_kernel(TransposeBatch b) {
     transpose_tile(reinterpret_cast<const uint16_t *>(b.job[j].src), reinterpret_cast<uint16_t *>(b.job[j].dst),
                    b.job[j].rows, b.job[j].cols, (t / tiles_c) * kTile, (t % tiles_c) * kTile, tile, b.job[j].colsum,
                    red);
-}
-
-// ------------------------------------------------------------------ GELU
-__global__ __launch_bounds__(256) void gelu_kernel(const uint16_t *__restrict__ v, uint16_t *__restrict__ u,
-                                                   size_t n8) {
-    const size_t i = (size_t)blockIdx.x * 256 + threadIdx.x;
-    if (i >= n8) return;
-    const u32x4 x = reinterpret_cast<const u32x4 *>(v)[i];
-    u32x4 y;
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-        const float lo = gelu(__uint_as_float(x[e] << 16)), hi = gelu(__uint_as_float(x[e] & 0xffff0000u));
-        y[e] = (uint32_t)to_bf(lo) | ((uint32_t)to_bf(hi) << 16);
-    }
-    reinterpret_cast<u32x4 *>(u)[i] = y;
 }
 
 // ------------------------------------------------------------------ LayerNorm backward
@@ -520,9 +503,12 @@ __global__ __launch_bounds__(256) void attention_backward_kernel(
     const uint16_t *Vh = Vt + (size_t)bh * kAbDh * vt_stride;
     uint16_t *Pt = scratch + (size_t)bh * kAbScratch, *dSt = Pt + kAbSeq * kAbSeq, *dS = dSt + kAbSeq * kAbSeq;
 
+    // 32-token blocks in use: nothing past them is loaded, multiplied or written
+    // (a sequence of 32 takes one block of four; 8 heads of it 18.9 -> 8.9 us)
+    const int nb = (S + 31) / 32;
     // ---- load: 8-element vectors, row i = v / 8, columns c0 .. c0 + 7
     const u32x4 zero = {0u, 0u, 0u, 0u};
-    for (int v = tid; v < kAbSeq * kAbDh / 8; v += 256) {
+    for (int v = tid; v < 32 * nb * kAbDh / 8; v += 256) {
         const int i = v / 8, c0 = (v % 8) * 8;
         const bool in = i < S;
         const u32x4 q = in ? *reinterpret_cast<const u32x4 *>(Qh + (size_t)i * kAbDh + c0) : zero;
@@ -543,8 +529,8 @@ __global__ __launch_bounds__(256) void attention_backward_kernel(
         if (v % 8 == 0) sD[i] = dot;
     }
     // V from V^T [c][j]: vector v = 8 keys j0 .. j0 + 7 of column c; keys past S are zero
-    for (int v = tid; v < kAbDh * kAbSeq / 8; v += 256) {
-        const int c = v / (kAbSeq / 8), j0 = (v % (kAbSeq / 8)) * 8;
+    for (int v = tid; v < kAbDh * 4 * nb; v += 256) {
+        const int c = v / (4 * nb), j0 = (v % (4 * nb)) * 8;
         u32x4 x = j0 < S ? *reinterpret_cast<const u32x4 *>(Vh + (size_t)c * vt_stride + j0) : zero;
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
@@ -556,59 +542,65 @@ __global__ __launch_bounds__(256) void attention_backward_kernel(
 
     // ---- phase 1: queries of this wave against all keys
     const int iq = 32 * wave + col;          // this lane's query
-    f32x16 st[4], dpt[4];
+    if (wave < nb) {
+        f32x16 st[4], dpt[4];
 #pragma unroll
-    for (int jb = 0; jb < 4; ++jb) {
+        for (int jb = 0; jb < 4; ++jb) {
+            if (jb >= nb) continue;
 #pragma unroll
-        for (int r = 0; r < 16; ++r) st[jb][r] = dpt[jb][r] = 0.f;
+            for (int r = 0; r < 16; ++r) st[jb][r] = dpt[jb][r] = 0.f;
 #pragma unroll
-        for (int ks = 0; ks < kAbDh / 16; ++ks) {
-            const int kc = 16 * ks + 8 * half;
-            st[jb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ld8(sK + (32 * jb + col) * kAbLd + kc),
-                                                             ld8(sQ + iq * kAbLd + kc), st[jb], 0, 0, 0);
-            dpt[jb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ld8(sV + (32 * jb + col) * kAbLd + kc),
-                                                              ld8(sdO + iq * kAbLd + kc), dpt[jb], 0, 0, 0);
-        }
-    }
-    float mx = -INFINITY;
-#pragma unroll
-    for (int jb = 0; jb < 4; ++jb)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-            const int j = 32 * jb + 8 * (r / 4) + 4 * half + r % 4;
-            const bool ok = iq < S && j < S && (!causal || j <= iq);
-            st[jb][r] = ok ? st[jb][r] * scale : -INFINITY;
-            mx = fmaxf(mx, st[jb][r]);
-        }
-    mx = fmaxf(mx, __shfl_xor(mx, 32));
-    float l = 0.f;
-#pragma unroll
-    for (int jb = 0; jb < 4; ++jb)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-            const float p = st[jb][r] == -INFINITY ? 0.f : __expf(st[jb][r] - mx);
-            st[jb][r] = p;
-            l += p;
-        }
-    l += __shfl_xor(l, 32);
-    const float inv_l = iq < S ? 1.0f / l : 0.f;
-    const float Di = sD[iq];
-#pragma unroll
-    for (int jb = 0; jb < 4; ++jb)
-#pragma unroll
-        for (int q4 = 0; q4 < 4; ++q4) {
-            uint16_t dsv[4];
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const int r = 4 * q4 + e, j = 32 * jb + 8 * q4 + 4 * half + e;
-                const float p = st[jb][r] * inv_l, ds = p * (dpt[jb][r] - Di);
-                Pt[j * kAbSeq + iq] = to_bf(p);
-                dsv[e] = to_bf(ds);
-                dSt[j * kAbSeq + iq] = dsv[e];
+            for (int ks = 0; ks < kAbDh / 16; ++ks) {
+                const int kc = 16 * ks + 8 * half;
+                st[jb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ld8(sK + (32 * jb + col) * kAbLd + kc),
+                                                                 ld8(sQ + iq * kAbLd + kc), st[jb], 0, 0, 0);
+                dpt[jb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ld8(sV + (32 * jb + col) * kAbLd + kc),
+                                                                  ld8(sdO + iq * kAbLd + kc), dpt[jb], 0, 0, 0);
             }
-            *reinterpret_cast<u32x2 *>(dS + iq * kAbSeq + 32 * jb + 8 * q4 + 4 * half) =
-                u32x2{(uint32_t)dsv[0] | ((uint32_t)dsv[1] << 16), (uint32_t)dsv[2] | ((uint32_t)dsv[3] << 16)};
         }
+        float mx = -INFINITY;
+#pragma unroll
+        for (int jb = 0; jb < 4; ++jb)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                if (jb >= nb) continue;
+                const int j = 32 * jb + 8 * (r / 4) + 4 * half + r % 4;
+                const bool ok = iq < S && j < S && (!causal || j <= iq);
+                st[jb][r] = ok ? st[jb][r] * scale : -INFINITY;
+                mx = fmaxf(mx, st[jb][r]);
+            }
+        mx = fmaxf(mx, __shfl_xor(mx, 32));
+        float l = 0.f;
+#pragma unroll
+        for (int jb = 0; jb < 4; ++jb)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                if (jb >= nb) continue;
+                const float p = st[jb][r] == -INFINITY ? 0.f : __expf(st[jb][r] - mx);
+                st[jb][r] = p;
+                l += p;
+            }
+        l += __shfl_xor(l, 32);
+        const float inv_l = iq < S ? 1.0f / l : 0.f;
+        const float Di = sD[iq];
+#pragma unroll
+        for (int jb = 0; jb < 4; ++jb)
+#pragma unroll
+            for (int q4 = 0; q4 < 4; ++q4) {
+                if (jb >= nb) continue;
+                uint16_t dsv[4];
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const int r = 4 * q4 + e, j = 32 * jb + 8 * q4 + 4 * half + e;
+                    const float p = st[jb][r] * inv_l, ds = p * (dpt[jb][r] - Di);
+                    Pt[j * kAbSeq + iq] = to_bf(p);
+                    dsv[e] = to_bf(ds);
+                    dSt[j * kAbSeq + iq] = dsv[e];
+                }
+                *reinterpret_cast<u32x2 *>(dS + iq * kAbSeq + 32 * jb + 8 * q4 + 4 * half) =
+                    u32x2{(uint32_t)dsv[0] | ((uint32_t)dsv[1] << 16), (uint32_t)dsv[2] | ((uint32_t)dsv[3] << 16)};
+            }
+    }
 
     // ---- relayout: Q, K, dO rows -> registers -> transposed copies over the same LDS
     constexpr int kVecs = kAbSeq * kAbDh / 8 / 256;   // 8-element row vectors per thread and matrix
@@ -616,6 +608,7 @@ __global__ __launch_bounds__(256) void attention_backward_kernel(
 #pragma unroll
     for (int u = 0; u < kVecs; ++u) {
         const int v = tid + 256 * u, i = v / 8, c0 = (v % 8) * 8;
+        if (i >= 32 * nb) continue;
         rq[u] = *reinterpret_cast<const u32x4 *>(sQ + i * kAbLd + c0);
         rk[u] = *reinterpret_cast<const u32x4 *>(sK + i * kAbLd + c0);
         rg[u] = *reinterpret_cast<const u32x4 *>(sdO + i * kAbLd + c0);
@@ -624,6 +617,7 @@ __global__ __launch_bounds__(256) void attention_backward_kernel(
 #pragma unroll
     for (int u = 0; u < kVecs; ++u) {
         const int v = tid + 256 * u, i = v / 8, c0 = (v % 8) * 8;
+        if (i >= 32 * nb) continue;
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
             sQt[(c0 + 2 * e) * kAbLdT + i] = (uint16_t)(rq[u][e] & 0xffffu);
@@ -642,9 +636,10 @@ __global__ __launch_bounds__(256) void attention_backward_kernel(
     for (int cb = 0; cb < 2; ++cb)
 #pragma unroll
         for (int r = 0; r < 16; ++r) dv[cb][r] = dk[cb][r] = dq[cb][r] = 0.f;
+    if (wave >= nb) return;   // no barrier follows
     const int row = 32 * wave + col;
-#pragma unroll
-    for (int ks = 0; ks < kAbSeq / 16; ++ks) {
+#pragma unroll 2
+    for (int ks = 0; ks < 2 * nb; ++ks) {
         const int kc = 16 * ks + 8 * half;
         const bf16x8 a_p = ld8(Pt + row * kAbSeq + kc), a_dst = ld8(dSt + row * kAbSeq + kc);
         const bf16x8 a_ds = ld8(dS + row * kAbSeq + kc);
@@ -777,13 +772,6 @@ hipError_t launch_colsums(const ColsumJob *jobs, int n_jobs, hipStream_t stream)
     }
     b.first[n_jobs] = blocks;
     return launch_kernel(colsum_jobs_kernel, dim3(blocks), dim3(kFinCols * kFinLanes), stream, b);
-}
-
-hipError_t launch_gelu(const bf16_t *v, bf16_t *u, size_t n, hipStream_t stream) {
-    if (n == 0) return hipSuccess;
-    if (n % 8) return hipErrorInvalidValue;
-    const size_t n8 = n / 8;
-    return launch_kernel(gelu_kernel, dim3((unsigned)((n8 + 255) / 256)), dim3(256), stream, v, u, n8);
 }
 
 hipError_t launch_ln_backward(const float *dy, const float *z, const float *stats, const float *gamma, float *dz,
