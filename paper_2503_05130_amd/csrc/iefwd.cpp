@@ -150,7 +150,7 @@ struct TrainState {
     iefwd_train_params hp{};
     uint64_t steps = 0;
     void *blob = nullptr;
-    float *loss_host = nullptr;                   // pinned: the last step's summed token losses
+    float *loss_host = nullptr;                   // pinned, written by the step's last sum: its summed token losses
     // optimiser state, segments in (layer, slot) order then the head
     float *master = nullptr, *grad = nullptr, *mom1 = nullptr, *mom2 = nullptr;
     size_t n_params = 0;                          // padded element count
@@ -173,7 +173,7 @@ struct TrainState {
     std::vector<Saved> saved;
     // backward scratch
     float *dxa = nullptr, *dxb = nullptr, *dz = nullptr, *xl = nullptr, *loss_t = nullptr, *dlogits = nullptr;
-    float *colpart = nullptr, *loss_sum = nullptr;   // column-sum partials of one layer; the loss
+    float *colpart = nullptr;                     // column-sum partials of one layer
     bf16_t *dzb = nullptr, *dzb1 = nullptr, *dvb = nullptr, *dctx = nullptr, *dqkv = nullptr;
     // transposed operands of a layer's weight gradients: dz2, u, dv, X1, dz1, ctx, dqkv, X
     bf16_t *tr[8] = {};
@@ -738,7 +738,6 @@ void train_alloc(iefwd_instance *I, const iefwd_train_params &hp) {
     // partial column sums of every bias / LayerNorm gradient of one layer (or of the head), each at most
     // [colpart_rows, n]
     const size_t o_colpart = reserve((size_t)colpart_rows((int)T, (int)d) * std::max(9 * d + F, no * d + no + 1) * 4);
-    const size_t o_lsum = reserve(4);
     const size_t o_dzb = reserve(T * d * 2), o_dvb = reserve(T * F * 2), o_dctx = reserve(T * d * 2);
     const size_t o_dqkv = reserve(T * 3 * d * 2), o_dzb1 = reserve(T * d * 2);
     const size_t tr_width[8] = {d, F, F, d, d, d, 3 * d, d};
@@ -772,7 +771,7 @@ void train_alloc(iefwd_instance *I, const iefwd_train_params &hp) {
                            f32(o.z1), f32(o.st1), f32(o.z2), f32(o.st2)});
     }
     t.dxa = f32(o_dxa); t.dxb = f32(o_dxb); t.dz = f32(o_dz); t.xl = f32(o_xl); t.loss_t = f32(o_loss);
-    t.dlogits = f32(o_dl); t.colpart = f32(o_colpart); t.loss_sum = f32(o_lsum);
+    t.dlogits = f32(o_dl); t.colpart = f32(o_colpart);
     t.dzb = b16(o_dzb); t.dvb = b16(o_dvb); t.dctx = b16(o_dctx); t.dqkv = b16(o_dqkv); t.dzb1 = b16(o_dzb1);
     for (int i = 0; i < 8; ++i) t.tr[i] = b16(o_tr[i]);
     t.zero_bias = b16(o_zero); t.attn_scratch = b16(o_ascr);
@@ -827,7 +826,7 @@ void train_alloc(iefwd_instance *I, const iefwd_train_params &hp) {
 
 // One training step on I->stream: forward with saved activations, loss, backward,
 // AdamW, then W^T refreshed.  x fp32 [B*S, d] and labels int32 [B*S] on the device.
-void train_run(iefwd_instance *I, const float *x) {
+void train_run(iefwd_instance *I, const float *x, const int32_t *labels) {
     TrainState &t = *I->train;
     const iefwd_config &c = I->cfg;
     const int B = (int)I->batch, S = (int)I->seq, T = B * S, d = (int)c.d_model, F = (int)c.d_ff;
@@ -850,10 +849,6 @@ void train_run(iefwd_instance *I, const float *x) {
     const int parts = colsum_partials(T), blocks64 = T / 64, ln_parts = ln_backward_partials(T, d);
     std::vector<ColsumJob> finals;
     auto region = [&](int col) { return t.colpart + (size_t)colpart_rows(T, d) * col; };
-    auto colsum = [&](const void *src, bool is_bf16, int n, float *dst, int col) {
-        bwd("column sums", [&] { return launch_colsum(src, is_bf16, region(col), T, n, 256, s); });
-        finals.push_back({region(col), dst, parts, n});
-    };
     auto flush_finals = [&] {
         bwd("column sums", [&] { return launch_colsums(finals.data(), (int)finals.size(), s); });
         finals.clear();
@@ -909,13 +904,16 @@ void train_run(iefwd_instance *I, const float *x) {
         const LayerWeights &w = I->layers[L - 1];
         const TrainState::Saved &sv = t.saved[L - 1];
         fwd(IEFWD_K_LN, "head + loss", [&] {
-            return launch_head_loss(sv.z2, w.g2, w.be2, I->wh, I->bh, t.labels, t.xl, sv.st2, I->out, t.loss_t,
+            return launch_head_loss(sv.z2, w.g2, w.be2, I->wh, I->bh, labels, t.xl, sv.st2, I->out, t.loss_t,
                                     t.dlogits, t.dxa, T, d, no, eps, 1.0f / (float)T, s);
         });
-        bwd("head partials", [&] { return launch_head_partials(t.dlogits, t.xl, region(0), T, d, no, s); });
+        bwd("head partials", [&] {
+            return launch_head_partials(t.dlogits, t.xl, t.loss_t, region(0), region(no * d), region(no * d + no), T, d,
+                                        no, s);
+        });
         finals.push_back({region(0), t.grad + t.off_wh, parts, no * d});
-        colsum(t.dlogits, false, no, t.grad + t.off_bh, no * d);
-        colsum(t.loss_t, false, 1, t.loss_sum, no * d + no);
+        finals.push_back({region(no * d), t.grad + t.off_bh, parts, no});
+        finals.push_back({region(no * d + no), t.loss_host, parts, 1});
         flush_finals();
     }
 
@@ -1010,7 +1008,6 @@ void train_run(iefwd_instance *I, const float *x) {
         const int n = (int)std::min(wjobs.size() - j, (size_t)kMaxTransposeJobs);
         launch(I, IEFWD_K_OPTIM, "transpose", [&] { return launch_transposes(wjobs.data() + j, n, s); });
     }
-    hip_check(hipMemcpyAsync(t.loss_host, t.loss_sum, 4, hipMemcpyDeviceToHost, s), "loss copy");
 }
 
 }  // namespace
@@ -1193,18 +1190,18 @@ int iefwd_train_step(iefwd_instance *inst, const float *x, const int32_t *labels
             inst->seq = seq;
             const size_t T = (size_t)batch * seq, n = T * inst->cfg.d_model;
             const float *xin = x;
-            const hipMemcpyKind kind = inputs_are_device ? hipMemcpyDeviceToDevice : hipMemcpyHostToDevice;
-            hip_check(hipMemcpyAsync(inst->train->labels, labels, T * 4, kind, inst->stream), "label copy");
+            const int32_t *lin = labels;   // device inputs stay valid until the step completes: read in place
             if (!inputs_are_device) {
+                lin = inst->train->labels;
+                hip_check(hipMemcpyAsync(inst->train->labels, labels, T * 4, hipMemcpyHostToDevice, inst->stream),
+                          "label copy");
                 hip_check(hipMemcpyAsync(inst->xstage, x, n * 4, hipMemcpyHostToDevice, inst->stream), "input copy");
                 xin = inst->xstage;
-            }
-            if (!inputs_are_device) {
                 hip_check(hipEventRecord(inst->ev_copy, inst->stream), "hipEventRecord");
                 hip_check(hipEventSynchronize(inst->ev_copy), "hipEventSynchronize");
             }
             hip_check(hipEventRecord(inst->ev_start, inst->stream), "hipEventRecord");
-            train_run(inst, xin);
+            train_run(inst, xin, lin);
             hip_check(hipEventRecord(inst->ev_end, inst->stream), "hipEventRecord");
             inst->state = iefwd_instance::State::InFlight;
             inst->have_batch = true;

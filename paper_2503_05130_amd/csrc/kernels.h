@@ -60,9 +60,6 @@ int ln_backward_partials(int rows, int d);
 hipError_t launch_ln_backward_params(const float *dy, const float *z, const float *stats, const float *gamma,
                                      float *dz, bf16_t *dzb, float *part_g, float *part_b, int rows, int d,
                                      hipStream_t stream);
-// dst[b][f] = sum of src[r][f] over rows b * rows_per_part .. (b + 1) * rows_per_part - 1, in row order.
-hipError_t launch_colsum(const void *src, bool src_bf16, float *dst, int rows, int n, int rows_per_part,
-                         hipStream_t stream);
 // Up to kMaxColsumJobs whole-column sums of fp32 [rows, n] matrices in one launch:
 // dst[f] = sum of src[r][f] over all rows, in a fixed order (8 interleaved row
 // lanes, each in row order, then the lanes in order).
@@ -81,9 +78,10 @@ hipError_t launch_head_loss(const float *z, const float *gamma, const float *bet
                             const bf16_t *bh, const int32_t *labels, float *xl, float *stats, float *logits,
                             float *loss_t, float *dlogits, float *dx, int rows, int d, int n_out, float eps,
                             float inv_n, hipStream_t stream);
-// part[b][c * d + f] = sum over chunk b's rows of dlogits[r][c] xl[r][f].
-hipError_t launch_head_partials(const float *dlogits, const float *xl, float *part, int rows, int d, int n_out,
-                                hipStream_t stream);
+// Over chunk b's rows: part[b][c * d + f] = sum dlogits[r][c] xl[r][f],
+// part_b[b][c] = sum dlogits[r][c], part_l[b] = sum loss_t[r].
+hipError_t launch_head_partials(const float *dlogits, const float *xl, const float *loss_t, float *part, float *part_b,
+                                float *part_l, int rows, int d, int n_out, hipStream_t stream);
 // Attention backward for seq <= 128, head_dim 64: from Q, K [B,H,S,dh], V^T
 // [B,H,dh,vt_stride], the forward's context and its gradient (bf16 [B*S, H*dh])
 // to dQ | dK | dV as bf16 [B*S, 3 H dh] (the QKV product's column order).

@@ -7,8 +7,8 @@
 //                      transposed activations); several in one launch; on
 //                      request also the per-64-row column sums of the source
 //                      (the bias gradients' first stage)
-//   colsum             per row block: column sums (fp32 or bf16 input), fixed
-//                      order; the last stages of several sums in one launch
+//   colsum             column sums of partial rows, fixed order: the last stages
+//                      of several sums in one launch
 //   ln_backward        dz = rstd (g - mean(g) - x^ mean(g x^)), g = dy gamma,
 //                      one wave per row, fp32; writes fp32 and bf16
 //   ln_param_partials  per 256-row chunk: sum dy x^ and sum dy per column
@@ -17,7 +17,8 @@
 //   head_loss          per token: the last LayerNorm, logits = X Wh^T + bh,
 //                      softmax cross-entropy, dlogits = (p - onehot) / N,
 //                      dX = dlogits Wh
-//   head_partials      per 256-row chunk: sum dlogits^T X (the head's gradient)
+//   head_partials      per 256-row chunk: sum dlogits^T X, dlogits and the losses
+//                      (the head's gradients and the loss)
 //   attention_backward per (batch, head), S <= 128, MFMA: P recomputed from Q
 //                      and K, dS = P (dP - D), D = rowsum(dO O); dQ, dK, dV
 //   adamw              one pass over every parameter (fp32 master, moments),
@@ -295,36 +296,6 @@ __global__ __launch_bounds__(256) void ln_param_partials_kernel(
     }
 }
 
-template <typename T>
-__device__ inline float load_as_f32(const T *p, size_t i);
-template <>
-__device__ inline float load_as_f32<float>(const float *p, size_t i) { return p[i]; }
-template <>
-__device__ inline float load_as_f32<uint16_t>(const uint16_t *p, size_t i) { return bf(p[i]); }
-
-// One workgroup's column block: dst[b * n + f] = sum of src rows b * rb ..
-// min(rows, b * rb + rb) - 1 of column f, f = 64 cb .. 64 cb + 63
-template <typename T>
-__device__ inline void colsum_block(const T *__restrict__ src, float *__restrict__ dst, int rows, int n, int rb,
-                                    int cb, int b, float (&red)[kColLanes][64]) {
-    const int c = threadIdx.x & 63, g = threadIdx.x >> 6, f = cb * 64 + c;
-    float s = 0.f;
-    if (f < n) {
-        const int r1 = min(rows, (b + 1) * rb);
-#pragma unroll 4
-        for (int r = b * rb + g; r < r1; r += kColLanes) s += load_as_f32(src, (size_t)r * n + f);
-    }
-    const float t = lane_total(s, c, g, red);
-    if (g == 0 && f < n) dst[(size_t)b * n + f] = t;
-}
-
-template <typename T>
-__global__ __launch_bounds__(256) void colsum_kernel(const T *__restrict__ src, float *__restrict__ dst, int rows,
-                                                     int n, int rb) {
-    __shared__ float red[kColLanes][64];
-    colsum_block(src, dst, rows, n, rb, blockIdx.x, blockIdx.y, red);
-}
-
 // Several whole-column sums in one launch (the last stage of a layer's sums:
 // a few hundred partial rows each).  Workgroup b takes 32 columns of job j
 // (first[j] <= b < first[j + 1]); thread (column c, lane g of 8) adds rows g,
@@ -461,21 +432,35 @@ __global__ __launch_bounds__(64 * kRowsPerBlock) void head_loss_kernel(
     }
 }
 
-// part[b][k * d + f] = sum over rows of chunk b of dlogits[r][k] * xl[r][f]
+// The head's column sums over the rows of chunk b, first stage, in one launch
+// (three took 9 us of a small step where one takes 4.7): columns k * d + f of
+// part sum dlogits[r][k] * xl[r][f], then columns of part_b dlogits[r][k], then
+// part_l the tokens' losses.
 __global__ __launch_bounds__(256) void head_partials_kernel(const float *__restrict__ dlogits,
-                                                            const float *__restrict__ xl, float *__restrict__ part,
+                                                            const float *__restrict__ xl,
+                                                            const float *__restrict__ loss_t, float *__restrict__ part,
+                                                            float *__restrict__ part_b, float *__restrict__ part_l,
                                                             int rows, int d, int n_out) {
     __shared__ float red[kColLanes][64];
     const int c = threadIdx.x & 63, g = threadIdx.x >> 6, idx = blockIdx.x * 64 + c, b = blockIdx.y;
+    const int r0 = b * kColRows + g, r1 = min(rows, (b + 1) * kColRows), nw = n_out * d;
     float s = 0.f;
-    if (idx < n_out * d) {
+    if (idx < nw) {
         const int k = idx / d, f = idx - k * d;
-        const int r1 = min(rows, (b + 1) * kColRows);
 #pragma unroll 4
-        for (int r = b * kColRows + g; r < r1; r += kColLanes) s += dlogits[(size_t)r * n_out + k] * xl[(size_t)r * d + f];
+        for (int r = r0; r < r1; r += kColLanes) s += dlogits[(size_t)r * n_out + k] * xl[(size_t)r * d + f];
+    } else if (idx < nw + n_out) {
+#pragma unroll 4
+        for (int r = r0; r < r1; r += kColLanes) s += dlogits[(size_t)r * n_out + (idx - nw)];
+    } else if (idx == nw + n_out) {
+#pragma unroll 4
+        for (int r = r0; r < r1; r += kColLanes) s += loss_t[r];
     }
     const float t = lane_total(s, c, g, red);
-    if (g == 0 && idx < n_out * d) part[(size_t)b * n_out * d + idx] = t;
+    if (g) return;
+    if (idx < nw) part[(size_t)b * nw + idx] = t;
+    else if (idx < nw + n_out) part_b[(size_t)b * n_out + (idx - nw)] = t;
+    else if (idx == nw + n_out) part_l[b] = t;
 }
 
 // ------------------------------------------------------------------ attention backward
@@ -843,17 +828,6 @@ hipError_t launch_ln_param_partials(const float *dy, const float *z, const float
                          dy, z, stats, part_g, part_b, rows, d);
 }
 
-hipError_t launch_colsum(const void *src, bool src_bf16, float *dst, int rows, int n, int rows_per_part,
-                         hipStream_t stream) {
-    if (rows <= 0) return hipSuccess;
-    const dim3 grid((n + 63) / 64, (rows + rows_per_part - 1) / rows_per_part);
-    if (src_bf16)
-        return launch_kernel(colsum_kernel<uint16_t>, grid, dim3(256), stream, static_cast<const uint16_t *>(src), dst,
-                             rows, n, rows_per_part);
-    return launch_kernel(colsum_kernel<float>, grid, dim3(256), stream, static_cast<const float *>(src), dst, rows, n,
-                         rows_per_part);
-}
-
 hipError_t launch_head_loss(const float *z, const float *gamma, const float *beta, const bf16_t *wh,
                             const bf16_t *bh, const int32_t *labels, float *xl, float *stats, float *logits,
                             float *loss_t, float *dlogits, float *dx, int rows, int d, int n_out, float eps,
@@ -865,11 +839,11 @@ hipError_t launch_head_loss(const float *z, const float *gamma, const float *bet
                          n_out, eps, inv_n);
 }
 
-hipError_t launch_head_partials(const float *dlogits, const float *xl, float *part, int rows, int d, int n_out,
-                                hipStream_t stream) {
+hipError_t launch_head_partials(const float *dlogits, const float *xl, const float *loss_t, float *part, float *part_b,
+                                float *part_l, int rows, int d, int n_out, hipStream_t stream) {
     if (rows <= 0) return hipSuccess;
-    return launch_kernel(head_partials_kernel, dim3((n_out * d + 63) / 64, colsum_partials(rows)), dim3(256), stream,
-                         dlogits, xl, part, rows, d, n_out);
+    return launch_kernel(head_partials_kernel, dim3((n_out * d + n_out + 1 + 63) / 64, colsum_partials(rows)), dim3(256),
+                         stream, dlogits, xl, loss_t, part, part_b, part_l, rows, d, n_out);
 }
 
 size_t attention_backward_scratch(int batch, int n_heads) { return (size_t)batch * n_heads * kAbScratch; }
