@@ -537,25 +537,33 @@ void pack_decode_weights(iefwd_instance *I) {
     const iefwd_config &c = I->cfg;
     const int d = (int)c.d_model, F = (int)c.d_ff;
     const int shape[4][2] = {{3 * d, d}, {d, d}, {F, d}, {d, F}};
-    bool used[4][3] = {};
-    for (int M = 1; M <= (int)std::min<uint32_t>(c.max_batch, 16); ++M) {
-        const bool ln = skinny_ln_fits(M, d);
-        for (int j = 0; j < 4; ++j) used[j][skinny_groups(M, shape[j][0], shape[j][1], ln && j % 2 == 0) / 2] = true;
-    }
-    size_t bytes = 0;
+    bool used[4][3];
+    size_t bytes;
     std::vector<size_t> offs;
-    for (uint32_t l = 0; l < c.n_layers; ++l)
-        for (int j = 0; j < 4; ++j)
-            for (int g = 0; g < 3; ++g) {
-                if (!used[j][g]) continue;
-                offs.push_back(bytes);
-                bytes = round_up(bytes + (size_t)shape[j][0] * shape[j][1] * 2, 256);
-            }
-    if (hipMalloc(&I->pblob, bytes) != hipSuccess) {
+    auto reserve = [&](int largest) {   // for steps of 1 .. largest sequences
+        std::memset(used, 0, sizeof used);
+        for (int M = 1; M <= largest; ++M) {
+            const bool ln = skinny_ln_fits(M, d);
+            for (int j = 0; j < 4; ++j) used[j][skinny_groups(M, shape[j][0], shape[j][1], ln && j % 2 == 0) / 2] = true;
+        }
+        bytes = 0;
+        offs.clear();
+        for (uint32_t l = 0; l < c.n_layers; ++l)
+            for (int j = 0; j < 4; ++j)
+                for (int g = 0; g < 3; ++g) {
+                    if (!used[j][g]) continue;
+                    offs.push_back(bytes);
+                    bytes = round_up(bytes + (size_t)shape[j][0] * shape[j][1] * 2, 256);
+                }
+        if (hipMalloc(&I->pblob, bytes) == hipSuccess) return true;
         (void)hipGetLastError();
         I->pblob = nullptr;
+        return false;
+    };
+    // where the copies of every class do not fit the device's memory, those of
+    // one sequence still may: a class without its copy reads row-major weights
+    if (!reserve((int)std::min<uint32_t>(c.max_batch, 16)) && !reserve(1))
         fail(IEFWD_ENOMEM, "device allocation of the packed decode weights failed");
-    }
     char *base = static_cast<char *>(I->pblob);
     size_t oi = 0;
     for (uint32_t l = 0; l < c.n_layers; ++l) {
