@@ -1,6 +1,5 @@
 // Fused softmax attention for gfx950: ctx = softmax(Q K^T / sqrt(dh) [+ causal]) V
-// per (batch, head), with an online softmax over 64-key chunks (32-key blocks
-// up to 128 positions).
+// per (batch, head), with an online softmax over 32-key blocks.
 //
 // Work split.  A workgroup of 4 waves owns 128 queries of one (batch, head);
 // each wave owns 32 of them.  Keys are streamed in 64-key chunks: the whole
@@ -28,12 +27,15 @@
 // What bounds it: the softmax's VALU work (32 exponentials a lane and chunk at a
 // quarter rate, then the sums and maxima), and where a CU holds one workgroup
 // the chain from the scores through the maximum to the context.  Hence both
-// 32-key blocks of a chunk at once with one maximum, the scale folded into the
-// exponent's fma, no rescale where no maximum rose, lane exchanges without
-// LDS, and V^T chunks stored in the fragments' key order.  Measured, before ->
-// after with the placement below: causal 16 heads x 4001 positions 100 -> 66 us,
-// 8 x 16 heads x 512 19.5 -> 14.2, 2 x 16 heads x 1024 of dim 128 34.7 -> 28.9.
-// Not kept: a second group of
+// 32-key blocks of a chunk side by side up to their exponentials, no rescale
+// where a block raises no maximum, lane exchanges without LDS, and V^T chunks
+// stored in the fragments' key order.  Measured, before -> after with the
+// placement below: causal 16 heads x 4001 positions 101 -> 74 us, 8 x 16 heads x
+// 512 20.1 -> 15.9, 2 x 16 heads x 1024 of dim 128 36.5 -> 32.2.  Not kept: one
+// maximum for a chunk's 64 keys and the scale in the exponent's fma (68, 14.9 and
+// 29.5 us), whose exponent at the largest score is the rounding error of
+// score * scale: past scores of 2^31 infinity or nothing, where the scaled and
+// rounded score less the maximum of such scores is exactly 0; a second group of
 // waves in the workgroup taking every other chunk (128 registers a lane, 14 of
 // them spilled: 8 x 16 x 512 19.6 us).
 //
@@ -77,7 +79,7 @@ __device__ inline float half_sum(float v) {
 // x * scale rounded on its own, whatever follows.
 __device__ inline float scaled(float x, float scale) {
     float y = x * scale;
-    asm volatile("" : "+v"(y));
+    asm("" : "+v"(y));
     return y;
 }
 
@@ -108,7 +110,7 @@ __device__ inline bool place(int i, int n_bh, int n_groups, int &group, int &bh)
     return bh < n_bh;
 }
 
-template <int DH, bool CAUSAL, bool SHORT>
+template <int DH, bool CAUSAL>
 __global__ __launch_bounds__(kThreads) void attention_kernel(
     const bf16_t *__restrict__ Q, const bf16_t *__restrict__ K, const bf16_t *__restrict__ Vt,
     bf16_t *__restrict__ ctx, int n_bh, int n_groups, int n_heads, int seq, int k_rows, int seq_pad,
@@ -210,11 +212,10 @@ __global__ __launch_bounds__(kThreads) void attention_kernel(
         if (c + 1 < n_chunks) gload(c + 1);
         const bf16_t *kb = lds + buf * (K_ELEMS + V_ELEMS);
         const bf16_t *vb = kb + K_ELEMS;
-        // NB 32-key blocks of the chunk from block b0 on at once: their products side
-        // by side, one maximum, one rescale
-        auto blocks = [&](auto nb, int b0) {
+        // the chunk's first NB 32-key blocks: their products and maxima side by side
+        auto blocks = [&](auto nb) {
             constexpr int NB = decltype(nb)::value;
-            const int k0 = c * kChunk + 32 * b0;
+            const int k0 = c * kChunk;
             // ---- S^T blocks (32 keys x 32 queries)
             f32x16 st[NB];
 #pragma unroll
@@ -226,7 +227,7 @@ __global__ __launch_bounds__(kThreads) void attention_kernel(
 #pragma unroll
                 for (int sb = 0; sb < NB; ++sb) {
                     const bf16x8 kf = as_bf16x8(*reinterpret_cast<const u32x4 *>(
-                        kb + ((b0 + sb) * 32 + col) * K_STRIDE + ks * 16 + half * 8));
+                        kb + (sb * 32 + col) * K_STRIDE + ks * 16 + half * 8));
                     st[sb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf, qf[ks], st[sb], 0, 0, 0);
                 }
             // key of accumulator entry r: k0 + 32 sb + 8 (r / 4) + 4 half + r % 4.  Only the
@@ -241,61 +242,62 @@ __global__ __launch_bounds__(kThreads) void attention_kernel(
                         if (key >= seq || (CAUSAL && key > query)) st[sb][r] = -INFINITY;
                     }
             }
-            if constexpr (SHORT) {
+            // m[sb]: the running maximum after block sb, of the scores as scaled and
+            // rounded -- the value the exponent subtracts it from, so that the largest
+            // score's exponent is exactly 0 at any magnitude
+            float m[NB];
 #pragma unroll
-                for (int r = 0; r < 16; ++r) st[0][r] = scaled(st[0][r], scale_log2e);
-            }
-            float mx = st[0][0];
-#pragma unroll
-            for (int sb = 0; sb < NB; ++sb)
-#pragma unroll
-                for (int r = 0; r < 16; ++r) mx = fmaxf(mx, st[sb][r]);
-            mx = half_max(mx);
-            if constexpr (!SHORT) mx *= scale_log2e;
-            const float m_new = fmaxf(m_run, mx);   // finite: key 0 is visible to every query
-            float alpha = 1.f;
-            // blocks that raise no query's maximum rescale nothing (times 1)
-            if (__any(m_new > m_run)) {
-                alpha = __builtin_amdgcn_exp2f(m_run - m_new);
-                m_run = m_new;
-#pragma unroll
-                for (int d = 0; d < DB; ++d)
-#pragma unroll
-                    for (int r = 0; r < 16; ++r) acc[d][r] *= alpha;
-            }
-            float psum[2] = {0.f, 0.f};
-#pragma unroll
-            for (int sb = 0; sb < NB; ++sb)
+            for (int sb = 0; sb < NB; ++sb) {
+                float mx = -INFINITY;
 #pragma unroll
                 for (int r = 0; r < 16; ++r) {
-                    st[sb][r] = __builtin_amdgcn_exp2f(SHORT ? st[sb][r] - m_run
-                                                             : __builtin_fmaf(st[sb][r], scale_log2e, -m_run));
-                    psum[SHORT ? 0 : r & 1] += st[sb][r];
+                    st[sb][r] = scaled(st[sb][r], scale_log2e);
+                    mx = fmaxf(mx, st[sb][r]);
                 }
-            l_run = __builtin_fmaf(l_run, alpha, SHORT ? psum[0] : psum[0] + psum[1]);
-            // ---- ctx^T += V^T P^T, 16-key steps
+                m[sb] = fmaxf(sb ? m[sb - 1] : m_run, half_max(mx));   // finite: key 0 is visible to every query
+            }
+            float psum[NB];
 #pragma unroll
-            for (int j = 0; j < 2 * NB; ++j) {
-                bf16x8 pf;   // P^T fragment: entries r = 8 (j % 2) .. + 7 of block j / 2
+            for (int sb = 0; sb < NB; ++sb) {
+                psum[sb] = 0.f;
 #pragma unroll
-                for (int e = 0; e < 8; ++e) pf[e] = (__bf16)st[j / 2][8 * (j % 2) + e];
-                // chunk-local keys 32 b0 + 16 j + 4 half + {0..3, 8..11}
+                for (int r = 0; r < 16; ++r) {
+                    st[sb][r] = __builtin_amdgcn_exp2f(st[sb][r] - m[sb]);
+                    psum[sb] += st[sb][r];
+                }
+            }
 #pragma unroll
-                for (int d = 0; d < DB; ++d) {
-                    const u32x4 v = *reinterpret_cast<const u32x4 *>(
-                        vb + (d * 32 + col) * kVtStride + 32 * b0 + 16 * j + 8 * half);
-                    acc[d] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(v), pf, acc[d], 0, 0, 0);
+            for (int sb = 0; sb < NB; ++sb) {
+                float alpha = 1.f;
+                // a block that raises no query's maximum rescales nothing (times 1)
+                if (__any(m[sb] > m_run)) {
+                    alpha = __builtin_amdgcn_exp2f(m_run - m[sb]);
+                    m_run = m[sb];
+#pragma unroll
+                    for (int d = 0; d < DB; ++d)
+#pragma unroll
+                        for (int r = 0; r < 16; ++r) acc[d][r] *= alpha;
+                }
+                l_run = __builtin_fmaf(l_run, alpha, psum[sb]);
+                // ---- ctx^T += V^T P^T, two 16-key steps
+#pragma unroll
+                for (int j = 0; j < 2; ++j) {
+                    bf16x8 pf;   // P^T fragment: entries r = 8 j .. 8 j + 7
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) pf[e] = (__bf16)st[sb][8 * j + e];
+                    // chunk-local keys 32 sb + 16 j + 4 half + {0..3, 8..11}
+#pragma unroll
+                    for (int d = 0; d < DB; ++d) {
+                        const u32x4 v = *reinterpret_cast<const u32x4 *>(
+                            vb + (d * 32 + col) * kVtStride + 32 * sb + 16 * j + 8 * half);
+                        acc[d] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(v), pf, acc[d], 0, 0, 0);
+                    }
                 }
             }
         };
         const int left = wave_active ? wave_key_end - c * kChunk : 0;   // wave-uniform
-        if constexpr (SHORT) {
-            if (left > 0) blocks(std::integral_constant<int, 1>{}, 0);
-            if (left > 32) blocks(std::integral_constant<int, 1>{}, 1);
-        } else {
-            if (left > 32) blocks(std::integral_constant<int, 2>{}, 0);
-            else if (left > 0) blocks(std::integral_constant<int, 1>{}, 0);
-        }
+        if (left > 32) blocks(std::integral_constant<int, 2>{});
+        else if (left > 0) blocks(std::integral_constant<int, 1>{});
         if (c + 1 < n_chunks) lstore(buf ^ 1);
         __syncthreads();
     }
@@ -325,14 +327,8 @@ hipError_t launch(const bf16_t *q, const bf16_t *k, const bf16_t *vt, bf16_t *ct
     const int bh = batch * n_heads;
     const dim3 grid(kXcds * ((bh + kXcds - 1) / kXcds) * groups), block(kThreads);
     const float scale_log2e = 1.4426950408889634f / sqrtf((float)DH);
-    // Up to 128 positions (every training step) the sums keep their order: a
-    // maximum per 32 keys and scores scaled before it, the bits such sequences have
-    // always had.  A 64-key step would save them 0.4 us of 8.1 (32 x 12 heads).
-    if (seq <= 128)
-        return launch_kernel(attention_kernel<DH, CAUSAL, true>, grid, block, s, q, k, vt, ctx, bh, groups, n_heads,
-                             seq, k_rows, vt_stride, scale_log2e);
-    return launch_kernel(attention_kernel<DH, CAUSAL, false>, grid, block, s, q, k, vt, ctx, bh, groups, n_heads,
-                         seq, k_rows, vt_stride, scale_log2e);
+    return launch_kernel(attention_kernel<DH, CAUSAL>, grid, block, s, q, k, vt, ctx, bh, groups, n_heads, seq, k_rows,
+                         vt_stride, scale_log2e);
 }
 
 }  // namespace
