@@ -78,6 +78,7 @@ SIGNATURES = {
     "iefwd_test_skinny_groups": (_i32, [_u32, _u32, _u32, _i32, ctypes.POINTER(_u32)]),
     "iefwd_test_gemm_qkv": (_i32, [_vp, _vp, _vp, _vp, _vp, _vp, _u32, _u32, _u32, _u32, _vp]),
     "iefwd_test_attention": (_i32, [_vp, _vp, _vp, _vp, _u32, _u32, _u32, _u32, _i32, _vp]),
+    "iefwd_test_attention_place": (_i32, [_u32, _u32, _i32, _u32, _vp, _sz, ctypes.POINTER(_u32)]),
     "iefwd_test_layernorm": (_i32, [_vp, _vp, _vp, _vp, _vp, _u32, _u32, _f32, _vp]),
     "iefwd_test_ln_head": (_i32, [_vp, _vp, _vp, _vp, _vp, _vp, _u32, _u32, _u32, _f32, _vp]),
     "iefwd_test_cu_probe": (_i32, [_vp, _u32, _vp]),
@@ -358,6 +359,17 @@ def test_gemm_qkv(a, w, bias, q, k, vt, batch, seq, d_model, n_heads, stream=Non
 def test_attention(q, k, vt, ctx, batch, n_heads, seq, head_dim, causal, stream=None) -> None:
     _check(lib().iefwd_test_attention(_ptr(q), _ptr(k), _ptr(vt), _ptr(ctx), batch, n_heads, seq, head_dim,
                                       1 if causal else 0, _stream(stream)), "iefwd_test_attention")
+
+
+def test_attention_place(pairs: int, groups: int, causal: bool, n_cu: int = 256) -> np.ndarray:
+    """int32 [grid, 2]: the (query group, batch * head pair) of each workgroup of the attention grid; -1: idle."""
+    grid = _u32()
+    args = (pairs, groups, 1 if causal else 0, n_cu)
+    _check(lib().iefwd_test_attention_place(*args, None, 0, ctypes.byref(grid)), "iefwd_test_attention_place")
+    out = np.empty((grid.value, 2), dtype=np.int32)
+    _check(lib().iefwd_test_attention_place(*args, out.ctypes.data, out.size, ctypes.byref(grid)),
+           "iefwd_test_attention_place")
+    return out
 
 
 def test_layernorm(z, gamma, beta, out_f32, out_bf16, rows, d, eps, stream=None) -> None:

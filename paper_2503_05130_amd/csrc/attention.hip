@@ -44,6 +44,7 @@
 // Determinism: fixed key-block order, fixed reduction tree, no atomics.
 #include <type_traits>
 
+#include "attention_place.h"
 #include "kernels.h"
 
 namespace iefwd {
@@ -85,36 +86,10 @@ __device__ inline float scaled(float x, float scale) {
 
 __device__ inline bf16x8 as_bf16x8(u32x4 v) { return __builtin_bit_cast(bf16x8, v); }
 
-// Workgroup i of the grid -> (query group, batch * head); false for a padding
-// workgroup.  Workgroups are dealt round-robin to the 8 XCDs: XCD x takes the
-// heads bh = 8 k + x with all their query groups, so that a head's K and V
-// are fetched into one L2 only.  A causal group's work grows with its index,
-// and an XCD's workgroups are mostly resident at once, one after the other on
-// each of its 32 CUs: they go heaviest first in rows of 32, every other row
-// reversed, which pairs heavy with light ones.  (With the groups of a head
-// next to each other, 4 groups put every heaviest one on two of the XCDs: 8 x
-// 16 heads x 512 positions 19.5 us against 16.0.)
-constexpr int kXcds = 8, kCusPerXcd = 32;
-
-template <bool CAUSAL>
-__device__ inline bool place(int i, int n_bh, int n_groups, int &group, int &bh) {
-    const int x = i % kXcds, p = i / kXcds;
-    const int heads = (n_bh + kXcds - 1) / kXcds, n = heads * n_groups;   // of this XCD, padding included
-    int s = p;                                                           // position in the order of falling work
-    if constexpr (CAUSAL) {
-        const int row = p / kCusPerXcd, first = row * kCusPerXcd, last = min(first + kCusPerXcd, n) - 1;
-        if (row & 1) s = last - (p - first);
-    }
-    group = n_groups - 1 - s / heads;
-    bh = (s % heads) * kXcds + x;
-    return bh < n_bh;
-}
-
 template <int DH, bool CAUSAL>
 __global__ __launch_bounds__(kThreads) void attention_kernel(
     const bf16_t *__restrict__ Q, const bf16_t *__restrict__ K, const bf16_t *__restrict__ Vt,
-    bf16_t *__restrict__ ctx, int n_bh, int n_groups, int n_heads, int seq, int k_rows, int seq_pad,
-    float scale_log2e) {
+    bf16_t *__restrict__ ctx, AttnPlace place, int n_heads, int seq, int k_rows, int seq_pad, float scale_log2e) {
     constexpr int KS = DH / 16;              // 16-wide k steps of the QK^T product
     constexpr int DB = DH / 32;              // 32-row dh blocks of the context accumulator
     constexpr int K_STRIDE = DH + 8;         // K chunk row (bf16): 16 consecutive rows in distinct banks
@@ -129,7 +104,7 @@ __global__ __launch_bounds__(kThreads) void attention_kernel(
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int half = lane >> 5, col = lane & 31;
     int qgroup, bh;
-    if (!place<CAUSAL>(blockIdx.x, n_bh, n_groups, qgroup, bh)) return;   // uniform over the workgroup
+    if (!place.at(blockIdx.x, CAUSAL, qgroup, bh)) return;   // uniform over the workgroup
     const int qg0 = qgroup * 32 * kWaves;
     const int q0 = qg0 + wave * 32;                      // this wave's first query
     const bf16_t *Qh = Q + (size_t)bh * seq * DH;
@@ -321,31 +296,29 @@ __global__ __launch_bounds__(kThreads) void attention_kernel(
 }
 
 template <int DH, bool CAUSAL>
-hipError_t launch(const bf16_t *q, const bf16_t *k, const bf16_t *vt, bf16_t *ctx, int batch,
+hipError_t launch(const bf16_t *q, const bf16_t *k, const bf16_t *vt, bf16_t *ctx, const AttnPlace &place,
                   int n_heads, int seq, int k_rows, int vt_stride, hipStream_t s) {
-    const int groups = (seq + 32 * kWaves - 1) / (32 * kWaves);
-    const int bh = batch * n_heads;
-    const dim3 grid(kXcds * ((bh + kXcds - 1) / kXcds) * groups), block(kThreads);
     const float scale_log2e = 1.4426950408889634f / sqrtf((float)DH);
-    return launch_kernel(attention_kernel<DH, CAUSAL>, grid, block, s, q, k, vt, ctx, bh, groups, n_heads, seq, k_rows,
-                         vt_stride, scale_log2e);
+    return launch_kernel(attention_kernel<DH, CAUSAL>, dim3(place.grid()), dim3(kThreads), s, q, k, vt, ctx, place,
+                         n_heads, seq, k_rows, vt_stride, scale_log2e);
 }
 
 }  // namespace
 
 hipError_t launch_attention(const bf16_t *q, const bf16_t *k, const bf16_t *vt, bf16_t *ctx,
                             int batch, int n_heads, int seq, int head_dim, bool causal,
-                            hipStream_t stream, int k_rows, int vt_stride) {
+                            hipStream_t stream, int k_rows, int vt_stride, int n_cu) {
     if (batch <= 0 || seq <= 0) return hipSuccess;
     if (k_rows <= 0) k_rows = seq;
     if (vt_stride <= 0) vt_stride = attn_seq_pad(seq);
     if (k_rows < seq || vt_stride < attn_seq_pad(seq) || vt_stride % 64 != 0) return hipErrorInvalidValue;
+    const AttnPlace place = attention_place(batch * n_heads, (seq + 32 * kWaves - 1) / (32 * kWaves), n_cu);
     if (head_dim == 64)
-        return causal ? launch<64, true>(q, k, vt, ctx, batch, n_heads, seq, k_rows, vt_stride, stream)
-                      : launch<64, false>(q, k, vt, ctx, batch, n_heads, seq, k_rows, vt_stride, stream);
+        return causal ? launch<64, true>(q, k, vt, ctx, place, n_heads, seq, k_rows, vt_stride, stream)
+                      : launch<64, false>(q, k, vt, ctx, place, n_heads, seq, k_rows, vt_stride, stream);
     if (head_dim == 128)
-        return causal ? launch<128, true>(q, k, vt, ctx, batch, n_heads, seq, k_rows, vt_stride, stream)
-                      : launch<128, false>(q, k, vt, ctx, batch, n_heads, seq, k_rows, vt_stride, stream);
+        return causal ? launch<128, true>(q, k, vt, ctx, place, n_heads, seq, k_rows, vt_stride, stream)
+                      : launch<128, false>(q, k, vt, ctx, place, n_heads, seq, k_rows, vt_stride, stream);
     return hipErrorInvalidValue;
 }
 

@@ -22,6 +22,7 @@
 
 #include "controller.h"
 #include "init_weights.h"
+#include "attention_place.h"
 #include "kernels.h"
 #include "quota.h"
 
@@ -360,7 +361,7 @@ void run_forward(iefwd_instance *I, const float *x, int decode_pos = -1) {
                 return launch_decode_attention(I->q, qd.k, qd.vt, I->ctx, B, H, decode_pos + 1, dh, qd.k_rows,
                                                qd.vt_stride, I->dec_partials, s);
             return launch_attention(I->q, qd.k, qd.vt, I->ctx, B, H, S, dh, c.causal != 0, s, qd.k_rows,
-                                    qd.vt_stride);
+                                    qd.vt_stride, n_cu);
         });
         launch(I, IEFWD_K_OUTPROJ, "out-proj gemm", [&] {
             return gemm(ln_resid ? Epi::BiasLnResidF32 : Epi::BiasResidF32, I->ctx, w, 1, w.bo, resid, dst, d, d,
@@ -878,7 +879,7 @@ void train_run(iefwd_instance *I, const float *x, const int32_t *labels) {
                                    nullptr, n_cu);
             });
         fwd(IEFWD_K_ATTN, "attention",
-            [&] { return launch_attention(sv.q, sv.k, sv.vt, sv.ctx, B, H, S, dh, causal, s, S, spad); });
+            [&] { return launch_attention(sv.q, sv.k, sv.vt, sv.ctx, B, H, S, dh, causal, s, S, spad, n_cu); });
         if (l == 0) {
             fwd(IEFWD_K_OUTPROJ, "out-proj gemm", [&] {
                 return launch_gemm(Epi::BiasResidF32, sv.ctx, w.wo, w.bo, x, sv.z1, T, d, d, nullptr, s,
@@ -1764,6 +1765,25 @@ int iefwd_test_attention(const void *q, const void *k, const void *vt, void *ctx
         hip_check(launch_attention((const bf16_t *)q, (const bf16_t *)k, (const bf16_t *)vt, (bf16_t *)ctx, (int)batch,
                                    (int)n_heads, (int)seq, (int)head_dim, causal != 0, (hipStream_t)stream),
                   "attention launch");
+    });
+}
+
+int iefwd_test_attention_place(uint32_t pairs, uint32_t groups, int causal, uint32_t n_cu, int32_t *out, size_t n,
+                               uint32_t *grid) {
+    return guarded([&] {
+        if (!grid) fail(IEFWD_EINVAL, "grid is NULL");
+        if (pairs == 0 || pairs > 65535 || groups == 0 || groups > 1024) fail(IEFWD_EINVAL, "pairs must be in [1, 65535], groups in [1, 1024]");
+        if (n_cu == 0 || n_cu > 1024) fail(IEFWD_EINVAL, "n_cu must be in [1, 1024]");
+        const AttnPlace place = attention_place((int)pairs, (int)groups, (int)n_cu);
+        *grid = (uint32_t)place.grid();
+        if (!out) return;
+        if (n != 2 * (size_t)*grid) fail(IEFWD_EINVAL, "n must be 2 * grid");
+        for (uint32_t i = 0; i < *grid; ++i) {
+            int group = -1, pair = -1;
+            if (!place.at((int)i, causal != 0, group, pair)) group = pair = -1;
+            out[2 * i] = group;
+            out[2 * i + 1] = pair;
+        }
     });
 }
 

@@ -11,9 +11,11 @@ namespace iefwd {
 // ctx bf16 [B, S, H*dh] from Q, K [B,H,S,dh] and V^T [B,H,dh,S_pad].
 // k_rows: rows of K per (batch, head) (0: seq); vt_stride: row stride of V^T
 // (0: seq rounded up to 64), so that K and V^T may live in a longer KV cache.
+// n_cu: the CUs the stream's mask enables; it may change where a workgroup
+// runs, never the result.
 hipError_t launch_attention(const bf16_t *q, const bf16_t *k, const bf16_t *vt, bf16_t *ctx,
                             int batch, int n_heads, int seq, int head_dim, bool causal,
-                            hipStream_t stream, int k_rows = 0, int vt_stride = 0);
+                            hipStream_t stream, int k_rows = 0, int vt_stride = 0, int n_cu = 256);
 
 // Attention of one new query per (batch, head) over keys 0 .. n_keys - 1 of a
 // KV cache: q bf16 [B, H, dh], K [B, H, k_rows, dh], V^T [B, H, dh, vt_stride];
