@@ -315,7 +315,7 @@ __device__ inline float row_sum(float v) {
 // (bias, residual rows) and, without the LayerNorm prologue, the activations
 // are requested before the weights, so that no load is left to start after
 // the weight stream has ended.
-constexpr int kSkinnyWaves = 8, kSkinnyUnroll = 8;   // waves: 16 for narrow products of 9-16 rows (skinny_waves)
+constexpr int kSkinnyWaves = 8, kSkinnyUnroll = 8;
 constexpr int kSkinnyLnElems = 16384;
 constexpr int kSkinnyCus = 256;              // MI355X compute units
 
@@ -433,12 +433,12 @@ struct SkinnyLn {
 
 // NVL: 0 = activations from a; 8 or 16 = LayerNorm prologue for K <= 2048 / 4096.
 // FRAG: p.w is the packed copy of W (skinny_pack) for this G.  U: K steps a
-// wave requests at once (skinny_unroll: the wave's share of the steps, up to 8).
-// NW: waves (skinny_waves).  TWO: 9-16 rows with the LayerNorm prologue.
-template <Epi EPI, int G, int NVL, bool FRAG, int U, int NW, bool TWO>
-__global__ __launch_bounds__(64 * NW) void skinny_kernel(GemmParams p) {
+// wave requests at once (skinny_unroll).  TWO: 9-16 rows with the LayerNorm
+// prologue.
+template <Epi EPI, int G, int NVL, bool FRAG, int U, bool TWO>
+__global__ __launch_bounds__(64 * kSkinnyWaves) void skinny_kernel(GemmParams p) {
     constexpr bool LNA = NVL > 0;
-    static_assert(!LNA || NW == kSkinnyWaves, "the prologue's row split");
+    constexpr int NW = kSkinnyWaves;
     constexpr int FPW = 16 / G, TPW = 16 / G;      // features and token columns per K-group
     constexpr int kPartBytes = (NW - 1) * 64 * 16;
     // the LayerNorm prologue's bf16 activation tile, later the waves' partial
@@ -569,11 +569,11 @@ __global__ __launch_bounds__(64 * NW) void skinny_kernel(GemmParams p) {
     }
 }
 
-template <int G, int NVL, bool FRAG, int U, int NW, bool TWO>
+template <int G, int NVL, bool FRAG, int U, bool TWO>
 hipError_t launch_skinny(Epi epi, const GemmParams &p, hipStream_t stream) {
-    const dim3 grid(p.N / (16 / G)), block(64 * NW);
+    const dim3 grid(p.N / (16 / G)), block(64 * kSkinnyWaves);
     switch (epi) {
-#define EPI(E) case E: return launch_kernel(skinny_kernel<E, G, NVL, FRAG, U, NW, TWO>, grid, block, stream, p);
+#define EPI(E) case E: return launch_kernel(skinny_kernel<E, G, NVL, FRAG, U, TWO>, grid, block, stream, p);
     EPI(Epi::BiasBf16) EPI(Epi::BiasGeluBf16) EPI(Epi::BiasResidF32) EPI(Epi::Qkv)
 #undef EPI
     case Epi::BiasLnResidF32:
@@ -584,44 +584,35 @@ hipError_t launch_skinny(Epi epi, const GemmParams &p, hipStream_t stream) {
     return hipErrorInvalidValue;
 }
 
-// Waves of a workgroup.  With one K-group (9-16 rows) a narrow product has few
-// workgroups (N / 16), each of which must pull its weights alone: 16 waves have
-// twice the requests in flight.  Wider than 2048 the workgroups fill the chip
-// and 8 waves leave room for the next one.  (16 rows x 4096 -> 1024: 11.1 -> 8.2
-// us with the packed copy; 1024 -> 1024 takes 4.6 us either way.)  Part of the summation
-// order, so it depends on N, K and the number of groups alone.
-int skinny_waves(int N, int K, int G, bool ln) {
-    return G == 1 && !ln && N / 16 <= kSkinnyCus / 2 && K >= 2048 ? 16 : kSkinnyWaves;
-}
-
 // K steps a wave requests at once: its share of the product's steps, rounded
-// up to a power of two, at most kSkinnyUnroll (more steps take more rounds)
-int skinny_unroll(int K, int G, int waves) {
-    const int per_wave = (K / G / 32 + waves - 1) / waves;
+// up to a power of two, at most kSkinnyUnroll (more steps take more rounds).
+// Not kept for narrow long products of 9-16 rows, whose few workgroups pull
+// their weights alone: 16 waves (another order of sums; 16 x 4096 -> 1024 8.35 ->
+// 7.96 us, but 16 x 2048 -> 2048 5.20 -> 5.50), 16 steps at once (8.35 -> 8.18, but
+// 16 x 8192 -> 2048 15.4 -> 17.5).
+int skinny_unroll(int K, int G) {
+    const int per_wave = (K / G / 32 + kSkinnyWaves - 1) / kSkinnyWaves;
     int u = 1;
     while (u < per_wave && u < kSkinnyUnroll) u *= 2;
     return u;
 }
 
-template <int G, int NVL, bool FRAG, int NW, bool TWO>
+template <int G, int NVL, bool FRAG, bool TWO>
 hipError_t launch_skinny_u(Epi epi, const GemmParams &p, hipStream_t stream) {
-    switch (skinny_unroll(p.K, G, NW)) {
-    case 1: return launch_skinny<G, NVL, FRAG, 1, NW, TWO>(epi, p, stream);
-    case 2: return launch_skinny<G, NVL, FRAG, 2, NW, TWO>(epi, p, stream);
-    case 4: return launch_skinny<G, NVL, FRAG, 4, NW, TWO>(epi, p, stream);
-    default: return launch_skinny<G, NVL, FRAG, 8, NW, TWO>(epi, p, stream);
+    switch (skinny_unroll(p.K, G)) {
+    case 1: return launch_skinny<G, NVL, FRAG, 1, TWO>(epi, p, stream);
+    case 2: return launch_skinny<G, NVL, FRAG, 2, TWO>(epi, p, stream);
+    case 4: return launch_skinny<G, NVL, FRAG, 4, TWO>(epi, p, stream);
+    default: return launch_skinny<G, NVL, FRAG, 8, TWO>(epi, p, stream);
     }
 }
 
 template <int G, int NVL, bool FRAG>
 hipError_t launch_skinny_v(Epi epi, const GemmParams &p, hipStream_t stream) {
-    if constexpr (G == 1 && NVL == 0) {
-        if (skinny_waves(p.N, p.K, G, false) == 16) return launch_skinny_u<G, NVL, FRAG, 16, false>(epi, p, stream);
-    }
     if constexpr (G == 1 && NVL == 8) {   // more than 8 rows have one K-group, and K <= 16384 / 9
-        if (p.M > 8) return launch_skinny_u<G, NVL, FRAG, kSkinnyWaves, true>(epi, p, stream);
+        if (p.M > 8) return launch_skinny_u<G, NVL, FRAG, true>(epi, p, stream);
     }
-    return launch_skinny_u<G, NVL, FRAG, kSkinnyWaves, false>(epi, p, stream);
+    return launch_skinny_u<G, NVL, FRAG, false>(epi, p, stream);
 }
 
 template <int NVL>

@@ -1,5 +1,5 @@
 """The decode product's forms for 9-16 rows (two rows a wave in the LayerNorm
-prologue, 16 waves for narrow long-K products) and the packed copies an instance
+prologue), the order of its sums over K and the packed copies an instance
 keeps for each class of decode batches (1-4, 5-8, 9-16 sequences)."""
 import numpy as np
 import pytest
@@ -16,8 +16,8 @@ pytestmark = pytest.mark.gpu
 
 @pytest.mark.parametrize("M,N,K,ln", [
     (9, 48, 128, True), (16, 3072, 1024, True), (13, 4096, 1024, True), (9, 384, 1792, True),
-    (9, 16, 2048, False), (16, 1024, 4096, False), (12, 2048, 2080, False),   # 16 waves
-    (16, 2064, 2048, False), (16, 1024, 2016, False),                         # 8 waves: too wide, too short
+    (9, 16, 2048, False), (16, 1024, 4096, False), (12, 2048, 2080, False),
+    (16, 2064, 2048, False), (16, 1024, 2016, False),
 ])
 def test_nine_to_sixteen_rows(M, N, K, ln):
     print(f"skinny M={M} N={N} K={K} ln={ln}", flush=True)
@@ -47,6 +47,34 @@ def test_nine_to_sixteen_rows(M, N, K, ln):
     tol = gemm_bound(y, f64(w), K) + extra + UBF * 1.01 * np.abs(ref) + 1e-6
     assert np.all(np.abs(f64(out) - ref) <= tol)
     assert torch.equal(out.view(torch.int16), out2.view(torch.int16))
+
+
+@pytest.mark.parametrize("M,N,K", [(16, 1024, 4096), (9, 2048, 2048), (16, 512, 2080), (16, 4096, 1024), (13, 48, 800)])
+def test_order_of_sums(M, N, K):
+    """One K-group: wave w of 8 adds the 32-wide K steps w, w + 8, ... in turn, then the waves' sums are added in
+    wave order, whatever N and K.  A feature has three terms, 2^30, s in 1 .. 63 and -2^30, in steps that order adds
+    one after the other: s is lost where it follows 2^30 (whose last place is 2^7) and stays where it comes last."""
+    assert ie.test_skinny_groups(M, N, K, False) == 1
+    print(f"skinny order M={M} N={N} K={K}", flush=True)
+    rng = np.random.default_rng(N + K)
+    small = rng.integers(1, 64, N).astype(np.float32)
+    lost = rng.random(N) < 0.5
+    v = np.zeros((N, K // 32), np.float32)
+    for f in range(N):
+        if rng.random() < 0.6:   # one wave's three steps
+            at = np.sort(rng.choice(np.arange(rng.integers(8), K // 32, 8), 3, replace=False))
+        else:                    # three waves' sums
+            at = np.sort(rng.choice(8, 3, replace=False)) + 8 * rng.integers(0, K // 256, 3)
+        v[f, at] = [2.0 ** 30, small[f], -2.0 ** 30] if lost[f] else [2.0 ** 30, -2.0 ** 30, small[f]]
+    w, a = torch.zeros((N, K), dtype=torch.bfloat16), torch.zeros((M, K), dtype=torch.bfloat16)
+    at = 32 * np.arange(K // 32) + rng.integers(0, 32, K // 32)
+    w[:, at], a[:, at] = torch.from_numpy(v).bfloat16(), 1.0
+    zero = torch.zeros((M, N), dtype=torch.float32, device=DEV)
+    out = torch.empty_like(zero)
+    ie.test_gemm_skinny(ie.EPI_BIAS_RESID_F32, to_dev(a), to_dev(w), torch.zeros(N, dtype=torch.bfloat16, device=DEV),
+                        zero, out, M, N, K)
+    sync()
+    assert np.array_equal(out.cpu().numpy(), np.broadcast_to(np.where(lost, 0, small), (M, N)))
 
 
 @pytest.mark.parametrize("batch", [3, 6, 16])
