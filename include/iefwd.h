@@ -85,11 +85,9 @@ typedef struct iefwd_config {
     uint32_t pre_ln;        /* 0 = post-LN (BERT-style), 1 = pre-LN + final LN */
     uint32_t causal;        /* 0 = bidirectional, 1 = causal mask */
     uint32_t kv_cache;      /* 1 = keep every layer's K and V for iefwd_decode (needs pre_ln = causal
-                               = 1 and max_seq <= 8192), and packed copies of the four weight
+                               = 1 and max_seq <= 8192), and a packed copy of the four weight
                                matrices per layer for the decode step (the weights' device memory
-                               roughly doubles; up to four times it from max_batch = 9 on, whose
-                               larger decode batches read copies of their own); 0 = prefill only
-                               (default) */
+                               roughly doubles); 0 = prefill only (default) */
     float    ln_eps;        /* LayerNorm epsilon (default 1e-5) */
     float    w_std;         /* std of weight matrices (default 0.02) */
     float    b_std;         /* std of biases (default 0: biases are zero) */
@@ -478,7 +476,7 @@ int iefwd_test_gemm_skinny(uint32_t epilogue, const void *a, const void *w, cons
  *   r = l % 16, c = l / 16, f = b * (16 / groups) + r % (16 / groups),
  *   k = (r / (16 / groups)) * (K / groups) + 32 s + 8 c,
  * so that each wave load instruction of the product reads 1 KB of
- * consecutive addresses.  Instances created with kv_cache = 1 keep such copies
+ * consecutive addresses.  Instances created with kv_cache = 1 keep such a copy
  * of their four matrices per layer. */
 int iefwd_test_skinny_pack(const void *w, void *dst, uint32_t N, uint32_t K, uint32_t groups, void *stream);
 
@@ -488,6 +486,15 @@ int iefwd_test_skinny_pack(const void *w, void *dst, uint32_t N, uint32_t K, uin
  * (iefwd_test_skinny_groups), else EINVAL.  Results equal
  * iefwd_test_gemm_skinny's bit for bit. */
 int iefwd_test_gemm_skinny_packed(uint32_t epilogue, const void *a, const void *w_packed, uint32_t groups,
+                                  const void *bias, const float *resid, void *out, uint32_t M, uint32_t N, uint32_t K,
+                                  const float *ln_z, const float *ln_gamma, const float *ln_beta, float ln_eps,
+                                  void *stream);
+
+/* The same with a copy made for `groups` K-groups, a multiple of the product's
+ * own count (EINVAL otherwise), as a decode step of several sequences reads the
+ * copy made for one: the results are those of iefwd_test_gemm_skinny, bit for
+ * bit. */
+int iefwd_test_gemm_skinny_shared(uint32_t epilogue, const void *a, const void *w_packed, uint32_t groups,
                                   const void *bias, const float *resid, void *out, uint32_t M, uint32_t N, uint32_t K,
                                   const float *ln_z, const float *ln_gamma, const float *ln_beta, float ln_eps,
                                   void *stream);

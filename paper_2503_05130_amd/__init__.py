@@ -75,6 +75,8 @@ SIGNATURES = {
     "iefwd_test_skinny_pack": (_i32, [_vp, _vp, _u32, _u32, _u32, _vp]),
     "iefwd_test_gemm_skinny_packed": (_i32, [_u32, _vp, _vp, _u32, _vp, _vp, _vp, _u32, _u32, _u32, _vp, _vp, _vp,
                                              _f32, _vp]),
+    "iefwd_test_gemm_skinny_shared": (_i32, [_u32, _vp, _vp, _u32, _vp, _vp, _vp, _u32, _u32, _u32, _vp, _vp, _vp,
+                                             _f32, _vp]),
     "iefwd_test_skinny_groups": (_i32, [_u32, _u32, _u32, _i32, ctypes.POINTER(_u32)]),
     "iefwd_test_gemm_qkv": (_i32, [_vp, _vp, _vp, _vp, _vp, _vp, _u32, _u32, _u32, _u32, _vp]),
     "iefwd_test_attention": (_i32, [_vp, _vp, _vp, _vp, _u32, _u32, _u32, _u32, _i32, _vp]),
@@ -342,6 +344,14 @@ def test_gemm_skinny_packed(epilogue, a, w_packed, groups, bias, resid, out, M, 
     _check(lib().iefwd_test_gemm_skinny_packed(epilogue, _ptr(a), _ptr(w_packed), groups, _ptr(bias), _ptr(resid),
                                                _ptr(out), M, N, K, _ptr(z), _ptr(g), _ptr(b), eps, _stream(stream)),
            "iefwd_test_gemm_skinny_packed")
+
+
+def test_gemm_skinny_shared(epilogue, a, w_packed, groups, bias, resid, out, M, N, K, ln=None, stream=None) -> None:
+    """test_gemm_skinny reading a packed copy of W made for `groups` K-groups, a multiple of the product's own."""
+    z, g, b, eps = ln if ln is not None else (None, None, None, 0.0)
+    _check(lib().iefwd_test_gemm_skinny_shared(epilogue, _ptr(a), _ptr(w_packed), groups, _ptr(bias), _ptr(resid),
+                                               _ptr(out), M, N, K, _ptr(z), _ptr(g), _ptr(b), eps, _stream(stream)),
+           "iefwd_test_gemm_skinny_shared")
 
 
 def test_skinny_groups(M, N, K, ln) -> int:

@@ -305,16 +305,21 @@ __device__ inline float row_sum(float v) {
 // M * K <= kSkinnyLnElems and K <= 4096.
 //
 // Weights come either row-major ([N, K]: one load instruction covers 16 rows
-// x 64 bytes) or packed (FRAG): a copy of W in which the 64 lanes' 16-byte
-// pieces of one (workgroup, K step) fragment are one contiguous 1 KB block,
-// in lane order, blocks ordered by workgroup then K step.  A load instruction
-// then reads 1 KB of consecutive addresses, which streams from HBM at the
-// rate of a plain copy; the fragments, the MFMAs and the summation order are
-// the same in both forms, so the results are bit-identical.  The packed copy
-// is specific to one K-group count G (skinny_pack).  The epilogue's operands
-// (bias, residual rows) and, without the LayerNorm prologue, the activations
-// are requested before the weights, so that no load is left to start after
-// the weight stream has ended.
+// x 64 bytes) or packed: a copy of W in which the 64 lanes' 16-byte pieces of
+// one (workgroup, K step) fragment are one contiguous 1 KB block, in lane
+// order, blocks ordered by workgroup then K step.  A load instruction then
+// reads 1 KB of consecutive addresses, which streams from HBM at the rate of a
+// plain copy; the fragments, the MFMAs and the summation order are the same in
+// both forms, so the results are bit-identical.  The packed copy is made for
+// one K-group count (skinny_pack).  A product of fewer groups, of a larger
+// batch, reads it in 64-byte pieces of 4 (2) blocks that lie next to each
+// other: less than its own copy would give and more than row-major weights (us
+// row-major / this / own copy: 16 x 4096 -> 1024 10.5 / 9.4 / 8.4, 16 x 8192 ->
+// 2048 19.0 / 17.4 / 15.5, 8 x 4096 -> 1024 6.2 / 5.7 / 5.2, 16 x 1024 -> 3072 with
+// LayerNorm 6.1 / 5.9 / 6.0), without that copy's memory.  The epilogue's
+// operands (bias, residual rows) and, without the LayerNorm prologue, the
+// activations are requested before the weights, so that no load is left to
+// start after the weight stream has ended.
 constexpr int kSkinnyWaves = 8, kSkinnyUnroll = 8;
 constexpr int kSkinnyLnElems = 16384;
 constexpr int kSkinnyCus = 256;              // MI355X compute units
@@ -432,10 +437,11 @@ struct SkinnyLn {
 };
 
 // NVL: 0 = activations from a; 8 or 16 = LayerNorm prologue for K <= 2048 / 4096.
-// FRAG: p.w is the packed copy of W (skinny_pack) for this G.  U: K steps a
+// Q: 0 = p.w is row-major; 1, 2, 4 = p.w is the packed copy of W (skinny_pack)
+// for G Q K-groups.  U: K steps a
 // wave requests at once (skinny_unroll).  TWO: 9-16 rows with the LayerNorm
 // prologue.
-template <Epi EPI, int G, int NVL, bool FRAG, int U, bool TWO>
+template <Epi EPI, int G, int NVL, int Q, int U, bool TWO>
 __global__ __launch_bounds__(64 * kSkinnyWaves) void skinny_kernel(GemmParams p) {
     constexpr bool LNA = NVL > 0;
     constexpr int NW = kSkinnyWaves;
@@ -456,10 +462,23 @@ __global__ __launch_bounds__(64 * kSkinnyWaves) void skinny_kernel(GemmParams p)
     const int grp = row / FPW;                                  // K-group of this lane's row and column
     const int wf_row = n0 + row % FPW, a_row = min(row % TPW, p.M - 1);
     const int steps = kg / 32;
-    // row-major: step s of this lane at wrow + 32 s; packed: at wrow + 512 s
-    constexpr int WSTEP = FRAG ? 512 : 32;
-    const bf16_t *wrow = FRAG ? p.w + (size_t)blockIdx.x * steps * 512 + lane * 8
-                              : p.w + (size_t)wf_row * p.K + grp * kg + chunk * 8;
+    // Step s of this lane: row-major at wrow + 32 s; in its own packed copy at
+    // wrow + 512 s; in the copy for Q times the K-groups, a block of which holds
+    // 16 / (G Q) features, step s is step s % (steps / Q) of that copy's K-group
+    // grp Q + s / (steps / Q), whose rows lie 16 / (G Q) pieces further on
+    constexpr int CPW = 16 / (G * (Q ? Q : 1));   // features of a block of the copy
+    const int csteps = Q > 1 ? steps / Q : steps;
+    const bf16_t *wrow = Q > 1    ? p.w + (size_t)(wf_row / CPW) * csteps * 512 +
+                                     (chunk * 16 + grp * Q * CPW + wf_row % CPW) * 8
+                         : Q == 1 ? p.w + (size_t)blockIdx.x * steps * 512 + lane * 8
+                                  : p.w + (size_t)wf_row * p.K + grp * kg + chunk * 8;
+    auto w_step = [&](int s) {
+        if constexpr (Q == 0) return s * 32;
+        int g = 0;
+#pragma unroll
+        for (int i = 1; i < Q; ++i) g += s >= i * csteps;
+        return (s - g * csteps) * 512 + g * CPW * 8;
+    };
     const bf16_t *arow = (LNA ? a_lds : p.a) + (size_t)a_row * (LNA ? p.K + 8 : p.K) + grp * kg + chunk * 8;
     f32x4 acc = {0.f, 0.f, 0.f, 0.f};
     // The epilogue's operands are fetched first.  Lane (fq, t) of wave 0
@@ -486,7 +505,7 @@ __global__ __launch_bounds__(64 * kSkinnyWaves) void skinny_kernel(GemmParams p)
     auto load_w = [&](int s0) {
 #pragma unroll
         for (int u = 0; u < U; ++u)
-            wf[u] = *reinterpret_cast<const bf16x8 *>(wrow + min(s0 + u * NW, steps - 1) * WSTEP);
+            wf[u] = *reinterpret_cast<const bf16x8 *>(wrow + w_step(min(s0 + u * NW, steps - 1)));
     };
     auto load_a = [&](int s0) {
 #pragma unroll
@@ -569,11 +588,11 @@ __global__ __launch_bounds__(64 * kSkinnyWaves) void skinny_kernel(GemmParams p)
     }
 }
 
-template <int G, int NVL, bool FRAG, int U, bool TWO>
+template <int G, int NVL, int Q, int U, bool TWO>
 hipError_t launch_skinny(Epi epi, const GemmParams &p, hipStream_t stream) {
     const dim3 grid(p.N / (16 / G)), block(64 * kSkinnyWaves);
     switch (epi) {
-#define EPI(E) case E: return launch_kernel(skinny_kernel<E, G, NVL, FRAG, U, TWO>, grid, block, stream, p);
+#define EPI(E) case E: return launch_kernel(skinny_kernel<E, G, NVL, Q, U, TWO>, grid, block, stream, p);
     EPI(Epi::BiasBf16) EPI(Epi::BiasGeluBf16) EPI(Epi::BiasResidF32) EPI(Epi::Qkv)
 #undef EPI
     case Epi::BiasLnResidF32:
@@ -597,30 +616,45 @@ int skinny_unroll(int K, int G) {
     return u;
 }
 
-template <int G, int NVL, bool FRAG, bool TWO>
+template <int G, int NVL, int Q, bool TWO>
 hipError_t launch_skinny_u(Epi epi, const GemmParams &p, hipStream_t stream) {
     switch (skinny_unroll(p.K, G)) {
-    case 1: return launch_skinny<G, NVL, FRAG, 1, TWO>(epi, p, stream);
-    case 2: return launch_skinny<G, NVL, FRAG, 2, TWO>(epi, p, stream);
-    case 4: return launch_skinny<G, NVL, FRAG, 4, TWO>(epi, p, stream);
-    default: return launch_skinny<G, NVL, FRAG, 8, TWO>(epi, p, stream);
+    case 1: return launch_skinny<G, NVL, Q, 1, TWO>(epi, p, stream);
+    case 2: return launch_skinny<G, NVL, Q, 2, TWO>(epi, p, stream);
+    case 4: return launch_skinny<G, NVL, Q, 4, TWO>(epi, p, stream);
+    default: return launch_skinny<G, NVL, Q, 8, TWO>(epi, p, stream);
     }
 }
 
-template <int G, int NVL, bool FRAG>
+template <int G, int NVL, int Q>
 hipError_t launch_skinny_v(Epi epi, const GemmParams &p, hipStream_t stream) {
     if constexpr (G == 1 && NVL == 8) {   // more than 8 rows have one K-group, and K <= 16384 / 9
-        if (p.M > 8) return launch_skinny_u<G, NVL, FRAG, true>(epi, p, stream);
+        if (p.M > 8) return launch_skinny_u<G, NVL, Q, true>(epi, p, stream);
     }
-    return launch_skinny_u<G, NVL, FRAG, false>(epi, p, stream);
+    return launch_skinny_u<G, NVL, Q, false>(epi, p, stream);
+}
+
+template <int G, int NVL>
+hipError_t launch_skinny_q(Epi epi, const GemmParams &p, int q, hipStream_t stream) {
+    switch (q) {
+    case 0: return launch_skinny_v<G, NVL, 0>(epi, p, stream);
+    case 1: return launch_skinny_v<G, NVL, 1>(epi, p, stream);
+    case 2:
+        if constexpr (G <= 2) return launch_skinny_v<G, NVL, 2>(epi, p, stream);
+        break;
+    case 4:
+        if constexpr (G == 1) return launch_skinny_v<G, NVL, 4>(epi, p, stream);
+        break;
+    }
+    return hipErrorInvalidValue;
 }
 
 template <int NVL>
-hipError_t launch_skinny_g(Epi epi, const GemmParams &p, int g, bool frag, hipStream_t stream) {
+hipError_t launch_skinny_g(Epi epi, const GemmParams &p, int g, int q, hipStream_t stream) {
     switch (g) {
-    case 1: return frag ? launch_skinny_v<1, NVL, true>(epi, p, stream) : launch_skinny_v<1, NVL, false>(epi, p, stream);
-    case 2: return frag ? launch_skinny_v<2, NVL, true>(epi, p, stream) : launch_skinny_v<2, NVL, false>(epi, p, stream);
-    case 4: return frag ? launch_skinny_v<4, NVL, true>(epi, p, stream) : launch_skinny_v<4, NVL, false>(epi, p, stream);
+    case 1: return launch_skinny_q<1, NVL>(epi, p, q, stream);
+    case 2: return launch_skinny_q<2, NVL>(epi, p, q, stream);
+    case 4: return launch_skinny_q<4, NVL>(epi, p, q, stream);
     }
     return hipErrorInvalidValue;
 }
@@ -685,10 +719,11 @@ hipError_t launch_gemm_skinny(Epi epi, const bf16_t *a, const bf16_t *w, const b
     if (qkv) p.qkv = *qkv;
     if (ln_in) p.lnin = *ln_in;
     const int g = skinny_groups(M, N, K, ln_in != nullptr);
-    const bool frag = w_packed && packed_groups == g;
-    if (frag) p.w = w_packed;
-    if (!ln_in) return launch_skinny_g<0>(epi, p, g, frag, stream);
-    return K <= 2048 ? launch_skinny_g<8>(epi, p, g, frag, stream) : launch_skinny_g<16>(epi, p, g, frag, stream);
+    // a copy for fewer groups than the product's is not read (rows wider than 2048, 5-8 of them)
+    const int q = w_packed && packed_groups % g == 0 ? packed_groups / g : 0;
+    if (q) p.w = w_packed;
+    if (!ln_in) return launch_skinny_g<0>(epi, p, g, q, stream);
+    return K <= 2048 ? launch_skinny_g<8>(epi, p, g, q, stream) : launch_skinny_g<16>(epi, p, g, q, stream);
 }
 
 }  // namespace iefwd

@@ -92,7 +92,8 @@ struct LnIn {
 // With ln_in the activations are LayerNorm(z), normalised in the kernel (then
 // `a` is unused); that needs skinny_ln_fits(M, K).  w_packed: W's packed copy
 // for packed_groups K-groups (launch_skinny_pack), read instead of w when the
-// product uses that many groups for this M (bit-identical results, faster).
+// product uses that many groups for this M, or a half or a quarter of them
+// (bit-identical results, faster).
 hipError_t launch_gemm_skinny(Epi epi, const bf16_t *a, const bf16_t *w, const bf16_t *bias,
                               const float *resid, void *out, int M, int N, int K, const QkvDst *qkv,
                               hipStream_t stream, const LnIn *ln_in = nullptr, const bf16_t *w_packed = nullptr,

@@ -137,9 +137,9 @@ struct LayerWeights {
     bf16_t *wqkv, *bqkv, *wo, *bo, *w1, *b1, *w2, *b2;   // matrices output-major [out, in]
     float *g1, *be1, *g2, *be2;
     // decode instances: packed copies of wqkv, wo, w1, w2 for the skinny
-    // product, one for each K-group count (1, 2, 4: index count / 2) that decode
-    // batches up to max_batch use
-    bf16_t *packed[4][3] = {};
+    // product, and the K-group count each copy is packed for
+    bf16_t *packed[4] = {nullptr, nullptr, nullptr, nullptr};
+    int packed_groups[4] = {0, 0, 0, 0};
 };
 
 // Training state of an instance created with iefwd_train_create: the flat
@@ -343,11 +343,9 @@ void run_forward(iefwd_instance *I, const float *x, int decode_pos = -1) {
     auto gemm = [&](Epi epi, const bf16_t *a, const LayerWeights &w, int j, const bf16_t *bias, const float *resid,
                     void *out, int N, int K, const QkvDst *qkv, const LnResid *ln_resid, const LnIn *ln_in = nullptr) {
         const bf16_t *wt = j == 0 ? w.wqkv : j == 1 ? w.wo : j == 2 ? w.w1 : w.w2;
-        if (skinny && !ln_resid) {
-            const int groups = skinny_groups(T, N, K, ln_in != nullptr);
-            return launch_gemm_skinny(epi, a, wt, bias, resid, out, T, N, K, qkv, s, ln_in, w.packed[j][groups / 2],
-                                      groups);
-        }
+        if (skinny && !ln_resid)
+            return launch_gemm_skinny(epi, a, wt, bias, resid, out, T, N, K, qkv, s, ln_in, w.packed[j],
+                                      w.packed_groups[j]);
         return launch_gemm(epi, a, wt, bias, resid, out, T, N, K, qkv, s, ln_resid, nullptr, n_cu);
     };
     auto attention_block = [&](int l, const bf16_t *y_bf16, const LayerWeights &w, const float *resid,
@@ -529,55 +527,42 @@ void upload_weights(iefwd_instance *I) {
     }
 }
 
-// Decode instances: packed copies of each layer's four matrices, one for every
-// K-group count that a decode step of 1 .. max_batch (at most 16) sequences
-// uses (with the pre-LN LayerNorm fused into the QKV and FFN-up products where
-// it fits).  From row-major weights the four products of a step of 16 sequences
-// and width 1024 took 30 us a layer, from the copies 26.
+// Decode instances: the packed copy of each layer's four matrices, for the
+// K-group count a decode step of one sequence uses (with the pre-LN LayerNorm
+// fused into the QKV and FFN-up products).  Steps of more sequences, whose
+// products use fewer groups, read the same copy: one for each count would cost
+// up to twice the weights' memory again, which instances beside this one need.
 void pack_decode_weights(iefwd_instance *I) {
     const iefwd_config &c = I->cfg;
     const int d = (int)c.d_model, F = (int)c.d_ff;
+    const bool ln = skinny_ln_fits(1, d);
     const int shape[4][2] = {{3 * d, d}, {d, d}, {F, d}, {d, F}};
-    bool used[4][3];
-    size_t bytes;
+    const bool fused[4] = {ln, false, ln, false};
+    size_t bytes = 0;
     std::vector<size_t> offs;
-    auto reserve = [&](int largest) {   // for steps of 1 .. largest sequences
-        std::memset(used, 0, sizeof used);
-        for (int M = 1; M <= largest; ++M) {
-            const bool ln = skinny_ln_fits(M, d);
-            for (int j = 0; j < 4; ++j) used[j][skinny_groups(M, shape[j][0], shape[j][1], ln && j % 2 == 0) / 2] = true;
+    for (uint32_t l = 0; l < c.n_layers; ++l)
+        for (int j = 0; j < 4; ++j) {
+            offs.push_back(bytes);
+            bytes = round_up(bytes + (size_t)shape[j][0] * shape[j][1] * 2, 256);
         }
-        bytes = 0;
-        offs.clear();
-        for (uint32_t l = 0; l < c.n_layers; ++l)
-            for (int j = 0; j < 4; ++j)
-                for (int g = 0; g < 3; ++g) {
-                    if (!used[j][g]) continue;
-                    offs.push_back(bytes);
-                    bytes = round_up(bytes + (size_t)shape[j][0] * shape[j][1] * 2, 256);
-                }
-        if (hipMalloc(&I->pblob, bytes) == hipSuccess) return true;
+    if (hipMalloc(&I->pblob, bytes) != hipSuccess) {
         (void)hipGetLastError();
         I->pblob = nullptr;
-        return false;
-    };
-    // where the copies of every class do not fit the device's memory, those of
-    // one sequence still may: a class without its copy reads row-major weights
-    if (!reserve((int)std::min<uint32_t>(c.max_batch, 16)) && !reserve(1))
         fail(IEFWD_ENOMEM, "device allocation of the packed decode weights failed");
+    }
     char *base = static_cast<char *>(I->pblob);
     size_t oi = 0;
     for (uint32_t l = 0; l < c.n_layers; ++l) {
         LayerWeights &w = I->layers[l];
         const bf16_t *src[4] = {w.wqkv, w.wo, w.w1, w.w2};
-        for (int j = 0; j < 4; ++j)
-            for (int g = 0; g < 3; ++g) {
-                if (!used[j][g]) continue;
-                bf16_t *dst = reinterpret_cast<bf16_t *>(base + offs[oi++]);
-                hip_check(launch_skinny_pack(src[j], dst, shape[j][0], shape[j][1], 1 << g, I->stream),
-                          "weight packing");
-                w.packed[j][g] = dst;
-            }
+        for (int j = 0; j < 4; ++j) {
+            const int N = shape[j][0], K = shape[j][1];
+            const int g = skinny_groups(1, N, K, fused[j]);
+            bf16_t *dst = reinterpret_cast<bf16_t *>(base + offs[oi++]);
+            hip_check(launch_skinny_pack(src[j], dst, N, K, g, I->stream), "weight packing");
+            w.packed[j] = dst;
+            w.packed_groups[j] = g;
+        }
     }
     hip_check(hipStreamSynchronize(I->stream), "hipStreamSynchronize");
 }
@@ -1666,23 +1651,34 @@ int iefwd_test_gemm_plan(uint32_t M, uint32_t N, uint32_t K, uint32_t align, uin
     });
 }
 
+namespace {
+
+// The operand checks of the decode-step product's test entry points.
+void check_skinny_args(uint32_t epilogue, const void *a, const void *w, const void *bias, const float *resid,
+                       const void *out, uint32_t M, uint32_t N, uint32_t K, const float *ln_z, const float *ln_gamma,
+                       const float *ln_beta) {
+    if (epilogue > IEFWD_EPI_BIAS_RESID_F32) fail(IEFWD_EINVAL, "unknown epilogue");
+    if (!w || !bias || !out) fail(IEFWD_EINVAL, "NULL pointer");
+    if (epilogue == IEFWD_EPI_BIAS_RESID_F32 && !resid) fail(IEFWD_EINVAL, "resid is NULL");
+    if (M == 0 || M > 16) fail(IEFWD_EINVAL, "M must be in [1, 16]");
+    if (N == 0 || N % 16 || K == 0 || K % 32) fail(IEFWD_EINVAL, "N must be a positive multiple of 16, K of 32");
+    if ((uint64_t)N * K >= (1ull << 31)) fail(IEFWD_EINVAL, "too large");
+    if (ln_z) {
+        if (!ln_gamma || !ln_beta) fail(IEFWD_EINVAL, "NULL LayerNorm parameters");
+        if (!skinny_ln_fits((int)M, (int)K)) fail(IEFWD_EINVAL, "the LayerNorm prologue needs K <= 4096 and M * K <= 16384");
+    } else if (!a) {
+        fail(IEFWD_EINVAL, "a is NULL");
+    }
+}
+
+}  // namespace
+
 int iefwd_test_gemm_skinny(uint32_t epilogue, const void *a, const void *w, const void *bias, const float *resid,
                            void *out, uint32_t M, uint32_t N, uint32_t K, const float *ln_z, const float *ln_gamma,
                            const float *ln_beta, float ln_eps, void *stream) {
     return guarded([&] {
-        if (epilogue > IEFWD_EPI_BIAS_RESID_F32) fail(IEFWD_EINVAL, "unknown epilogue");
-        if (!w || !bias || !out) fail(IEFWD_EINVAL, "NULL pointer");
-        if (epilogue == IEFWD_EPI_BIAS_RESID_F32 && !resid) fail(IEFWD_EINVAL, "resid is NULL");
-        if (M == 0 || M > 16) fail(IEFWD_EINVAL, "M must be in [1, 16]");
-        if (N == 0 || N % 16 || K == 0 || K % 32) fail(IEFWD_EINVAL, "N must be a positive multiple of 16, K of 32");
-        if ((uint64_t)N * K >= (1ull << 31)) fail(IEFWD_EINVAL, "too large");
+        check_skinny_args(epilogue, a, w, bias, resid, out, M, N, K, ln_z, ln_gamma, ln_beta);
         LnIn lnin{ln_z, ln_gamma, ln_beta, ln_eps};
-        if (ln_z) {
-            if (!ln_gamma || !ln_beta) fail(IEFWD_EINVAL, "NULL LayerNorm parameters");
-            if (!skinny_ln_fits((int)M, (int)K)) fail(IEFWD_EINVAL, "the LayerNorm prologue needs K <= 4096 and M * K <= 16384");
-        } else if (!a) {
-            fail(IEFWD_EINVAL, "a is NULL");
-        }
         hip_check(launch_gemm_skinny((Epi)epilogue, (const bf16_t *)a, (const bf16_t *)w, (const bf16_t *)bias, resid,
                                      out, (int)M, (int)N, (int)K, nullptr, (hipStream_t)stream,
                                      ln_z ? &lnin : nullptr),
@@ -1707,21 +1703,27 @@ int iefwd_test_gemm_skinny_packed(uint32_t epilogue, const void *a, const void *
                                   const float *ln_z, const float *ln_gamma, const float *ln_beta, float ln_eps,
                                   void *stream) {
     return guarded([&] {
-        if (epilogue > IEFWD_EPI_BIAS_RESID_F32) fail(IEFWD_EINVAL, "unknown epilogue");
-        if (!w_packed || !bias || !out) fail(IEFWD_EINVAL, "NULL pointer");
-        if (epilogue == IEFWD_EPI_BIAS_RESID_F32 && !resid) fail(IEFWD_EINVAL, "resid is NULL");
-        if (M == 0 || M > 16) fail(IEFWD_EINVAL, "M must be in [1, 16]");
-        if (N == 0 || N % 16 || K == 0 || K % 32) fail(IEFWD_EINVAL, "N must be a positive multiple of 16, K of 32");
-        if ((uint64_t)N * K >= (1ull << 31)) fail(IEFWD_EINVAL, "too large");
+        check_skinny_args(epilogue, a, w_packed, bias, resid, out, M, N, K, ln_z, ln_gamma, ln_beta);
         LnIn lnin{ln_z, ln_gamma, ln_beta, ln_eps};
-        if (ln_z) {
-            if (!ln_gamma || !ln_beta) fail(IEFWD_EINVAL, "NULL LayerNorm parameters");
-            if (!skinny_ln_fits((int)M, (int)K)) fail(IEFWD_EINVAL, "the LayerNorm prologue needs K <= 4096 and M * K <= 16384");
-        } else if (!a) {
-            fail(IEFWD_EINVAL, "a is NULL");
-        }
         if ((int)groups != skinny_groups((int)M, (int)N, (int)K, ln_z != nullptr))
             fail(IEFWD_EINVAL, "the product uses another K-group count for this M, N, K");
+        hip_check(launch_gemm_skinny((Epi)epilogue, (const bf16_t *)a, (const bf16_t *)w_packed, (const bf16_t *)bias,
+                                     resid, out, (int)M, (int)N, (int)K, nullptr, (hipStream_t)stream,
+                                     ln_z ? &lnin : nullptr, (const bf16_t *)w_packed, (int)groups),
+                  "skinny gemm launch");
+    });
+}
+
+int iefwd_test_gemm_skinny_shared(uint32_t epilogue, const void *a, const void *w_packed, uint32_t groups,
+                                  const void *bias, const float *resid, void *out, uint32_t M, uint32_t N, uint32_t K,
+                                  const float *ln_z, const float *ln_gamma, const float *ln_beta, float ln_eps,
+                                  void *stream) {
+    return guarded([&] {
+        check_skinny_args(epilogue, a, w_packed, bias, resid, out, M, N, K, ln_z, ln_gamma, ln_beta);
+        const int own = skinny_groups((int)M, (int)N, (int)K, ln_z != nullptr);
+        if ((groups != 1 && groups != 2 && groups != 4) || (int)groups % own || K % (32 * groups))
+            fail(IEFWD_EINVAL, "the product cannot read a copy for this K-group count");
+        const LnIn lnin{ln_z, ln_gamma, ln_beta, ln_eps};
         hip_check(launch_gemm_skinny((Epi)epilogue, (const bf16_t *)a, (const bf16_t *)w_packed, (const bf16_t *)bias,
                                      resid, out, (int)M, (int)N, (int)K, nullptr, (hipStream_t)stream,
                                      ln_z ? &lnin : nullptr, (const bf16_t *)w_packed, (int)groups),

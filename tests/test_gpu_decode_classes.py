@@ -1,6 +1,6 @@
 """The decode product's forms for 9-16 rows (two rows a wave in the LayerNorm
-prologue), the order of its sums over K and the packed copies an instance
-keeps for each class of decode batches (1-4, 5-8, 9-16 sequences)."""
+prologue), the order of its sums over K, and the packed copy made for one sequence
+as larger decode batches (5-8 and 9-16 sequences) read it."""
 import numpy as np
 import pytest
 import torch
@@ -75,6 +75,59 @@ def test_order_of_sums(M, N, K):
                         zero, out, M, N, K)
     sync()
     assert np.array_equal(out.cpu().numpy(), np.broadcast_to(np.where(lost, 0, small), (M, N)))
+
+
+@pytest.mark.parametrize("epi", [ie.EPI_BIAS_BF16, ie.EPI_BIAS_GELU_BF16, ie.EPI_BIAS_RESID_F32])
+@pytest.mark.parametrize("M,N,K,groups,ln", [
+    (16, 1024, 1024, 4, False), (9, 48, 128, 4, False), (16, 1024, 4096, 2, False), (13, 64, 4224, 4, False),
+    (8, 1024, 4096, 4, False), (5, 48, 256, 4, False),          # 2 groups read the copy for 4
+    (16, 3072, 1024, 2, True), (9, 384, 1792, 4, True), (7, 384, 2176, 4, True), (6, 512, 640, 4, True),
+])
+def test_copy_for_more_groups(M, N, K, groups, ln, epi):
+    """A product reads a copy made for two or four times its K-groups to the same bits as row-major weights."""
+    own = ie.test_skinny_groups(M, N, K, ln)
+    print(f"skinny copy M={M} N={N} K={K} own={own} copy={groups} ln={ln} epi={epi}", flush=True)
+    assert groups in (2 * own, 4 * own)
+    rng = np.random.default_rng(M + N + K + epi)
+    w_d, b_d = to_dev(bf16_round(rng.standard_normal((N, K)) * 0.05)), to_dev(bf16_round(rng.standard_normal(N) * 0.1))
+    z, g, be, r = (torch.from_numpy(rng.standard_normal(s).astype(np.float32)).to(DEV) for s in ((M, K), K, K, (M, N)))
+    lnarg, a_d = ((z, g, be, 1e-5), None) if ln else (None, z.bfloat16())
+    fp32 = epi == ie.EPI_BIAS_RESID_F32
+    want = torch.full((M, N), float("nan"), dtype=torch.float32 if fp32 else torch.bfloat16, device=DEV)
+    got = torch.full_like(want, float("nan"))
+    packed = torch.empty(N * K, dtype=torch.bfloat16, device=DEV)
+    ie.test_skinny_pack(w_d, packed, N, K, groups)
+    ie.test_gemm_skinny(epi, a_d, w_d, b_d, r if fp32 else None, want, M, N, K, ln=lnarg)
+    ie.test_gemm_skinny_shared(epi, a_d, packed, groups, b_d, r if fp32 else None, got, M, N, K, ln=lnarg)
+    sync()
+    bits = torch.int32 if fp32 else torch.int16
+    assert torch.all(torch.isfinite(want)) and torch.equal(got.view(bits), want.view(bits))
+
+
+def test_copy_for_other_groups_is_refused():
+    w = torch.zeros((2048, 2048), dtype=torch.bfloat16, device=DEV)
+    b, a = torch.zeros(2048, dtype=torch.bfloat16, device=DEV), torch.zeros((8, 2048), dtype=torch.bfloat16, device=DEV)
+    out = torch.zeros((8, 2048), dtype=torch.bfloat16, device=DEV)
+    assert ie.test_skinny_groups(8, 2048, 2048, False) == 2
+    for groups in (1, 3, 8):
+        with pytest.raises(ie.IefwdError) as e:
+            ie.test_gemm_skinny_shared(ie.EPI_BIAS_BF16, a, w, groups, b, None, out, 8, 2048, 2048)
+        assert e.value.status == ie.EINVAL
+
+
+def test_decode_weights_take_one_copy():
+    """An instance's device memory holds one packed copy of its matrices, whatever max_batch: the same tokens in
+    16 sequences take no more than in 4, but for the decode attention's partial results (under 8 MB here)."""
+    shape = W.model_shape("decoder_l24_d1024_s512", n_layers=4, n_out=0)
+    used = []
+    for batch, seq in ((4, 256), (4, 256), (16, 64)):   # the first one also allocates what the process keeps
+        sync()
+        before = torch.cuda.mem_get_info()[0]
+        with ie.Instance(**dict(instance_config(shape, batch, seq), kv_cache=1)):
+            used.append(before - torch.cuda.mem_get_info()[0])
+    print(f"decode instance bytes: {used}", flush=True)
+    matrices = 4 * 12 * 1024 * 1024 * 2
+    assert 2 * matrices <= used[1] and used[2] - used[1] <= (24 << 20), used
 
 
 @pytest.mark.parametrize("batch", [3, 6, 16])
