@@ -175,9 +175,8 @@ struct TrainState {
     // backward scratch
     float *dxa = nullptr, *dxb = nullptr, *dz = nullptr, *xl = nullptr, *loss_t = nullptr, *dlogits = nullptr;
     float *colpart = nullptr;                     // column-sum partials of one layer
-    bf16_t *dzb = nullptr, *dzb1 = nullptr, *dvb = nullptr, *dctx = nullptr, *dqkv = nullptr;
-    // transposed operands of a layer's weight gradients: dz2, u, dv, X1, dz1, ctx, dqkv, X
-    bf16_t *tr[8] = {};
+    bf16_t *dzb = nullptr, *dvb = nullptr, *dctx = nullptr, *dqkv = nullptr;
+    bf16_t *ta = nullptr, *tb = nullptr;          // two of a layer's eight transposed operands
     bf16_t *zero_bias = nullptr, *attn_scratch = nullptr;
     int32_t *labels = nullptr;
 
@@ -733,10 +732,7 @@ void train_alloc(iefwd_instance *I, const iefwd_train_params &hp) {
     // [colpart_rows, n]
     const size_t o_colpart = reserve((size_t)colpart_rows((int)T, (int)d) * std::max(9 * d + F, no * d + no + 1) * 4);
     const size_t o_dzb = reserve(T * d * 2), o_dvb = reserve(T * F * 2), o_dctx = reserve(T * d * 2);
-    const size_t o_dqkv = reserve(T * 3 * d * 2), o_dzb1 = reserve(T * d * 2);
-    const size_t tr_width[8] = {d, F, F, d, d, d, 3 * d, d};
-    size_t o_tr[8];
-    for (int i = 0; i < 8; ++i) o_tr[i] = reserve(tr_width[i] * T * 2);
+    const size_t o_dqkv = reserve(T * 3 * d * 2), o_ta = reserve(wide * T * 2), o_tb = reserve(wide * T * 2);
     const size_t o_zero = reserve(wide * 2), o_lab = reserve(T * 4);
     const size_t o_ascr = reserve(attention_backward_scratch((int)c.max_batch, (int)c.n_heads) * 2);
     if (hipMalloc(&t.blob, bytes) != hipSuccess) {
@@ -766,9 +762,8 @@ void train_alloc(iefwd_instance *I, const iefwd_train_params &hp) {
     }
     t.dxa = f32(o_dxa); t.dxb = f32(o_dxb); t.dz = f32(o_dz); t.xl = f32(o_xl); t.loss_t = f32(o_loss);
     t.dlogits = f32(o_dl); t.colpart = f32(o_colpart);
-    t.dzb = b16(o_dzb); t.dvb = b16(o_dvb); t.dctx = b16(o_dctx); t.dqkv = b16(o_dqkv); t.dzb1 = b16(o_dzb1);
-    for (int i = 0; i < 8; ++i) t.tr[i] = b16(o_tr[i]);
-    t.zero_bias = b16(o_zero); t.attn_scratch = b16(o_ascr);
+    t.dzb = b16(o_dzb); t.dvb = b16(o_dvb); t.dctx = b16(o_dctx); t.dqkv = b16(o_dqkv); t.ta = b16(o_ta);
+    t.tb = b16(o_tb); t.zero_bias = b16(o_zero); t.attn_scratch = b16(o_ascr);
     t.labels = reinterpret_cast<int32_t *>(b + o_lab);
 
     // segments: where each tensor's updated value goes (the forward's copy)
@@ -928,6 +923,15 @@ void train_run(iefwd_instance *I, const float *x, const int32_t *labels) {
         const TrainState::Saved &sv = t.saved[l];
         const TrainState::Transposed &wt = t.wt[l];
         const auto &o = t.off[l];
+        // Of the layer's saved activations only the four weight-gradient operands (hb, ctx, h1b, u) are
+        // needed to the end.  What its backward has read last takes dz1 and the operands' transposes: z2
+        // (after LN2) dz1 and X^T, v (after dv) u^T, z1 (after LN1) dz1^T and ctx^T, q and k (after the
+        // attention) dz2^T and X1^T; dv^T and dqkv^T have the scratch.
+        const size_t Td = (size_t)T * d;
+        bf16_t *const z1_free = reinterpret_cast<bf16_t *>(sv.z1), *const z2_free = reinterpret_cast<bf16_t *>(sv.z2);
+        bf16_t *const dz1 = z2_free, *const xt = z2_free + Td, *const ut = sv.v, *const dz1t = z1_free,
+                      *const ctxt = z1_free + Td, *const dz2t = sv.q, *const x1t = sv.k, *const dvt = t.ta,
+                      *const dqkvt = t.tb;
         // LN2: dz2 (fp32 in dz, bf16 in dzb)
         ln_backward(t.dxa, sv.z2, sv.st2, w.g2, t.dzb, o[10], o[11], c_ln2);
         // FFN-down: dv = (dz2 W2) GELU'(v)
@@ -940,11 +944,11 @@ void train_run(iefwd_instance *I, const float *x, const int32_t *labels) {
             return launch_gemm(Epi::BiasResidF32, t.dvb, wt.w1, t.zero_bias, t.dz, t.dxb, T, d, F, nullptr, s,
                                nullptr, nullptr, n_cu);
         });
-        // LN1: dz1 (fp32 in dz, bf16 in dzb1)
-        ln_backward(t.dxb, sv.z1, sv.st1, w.g1, t.dzb1, o[4], o[5], c_ln1);
+        // LN1: dz1 (fp32 in dz, bf16)
+        ln_backward(t.dxb, sv.z1, sv.st1, w.g1, dz1, o[4], o[5], c_ln1);
         // out-projection: dctx = dz1 Wo
         bwd_gemm("dctx gemm", [&] {
-            return launch_gemm(Epi::BiasBf16, t.dzb1, wt.wo, t.zero_bias, nullptr, t.dctx, T, d, d, nullptr, s,
+            return launch_gemm(Epi::BiasBf16, dz1, wt.wo, t.zero_bias, nullptr, t.dctx, T, d, d, nullptr, s,
                                nullptr, nullptr, n_cu);
         });
         // attention
@@ -960,17 +964,17 @@ void train_run(iefwd_instance *I, const float *x, const int32_t *labels) {
             });
         // weight gradients of the layer, dW = dC^T A: all eight operands transposed in one launch (with the
         // bias gradients' first stages), the four products in another
-        transposes({{t.dzb, t.tr[0], T, d, region(c_b2)}, {sv.u, t.tr[1], T, F},
-                    {t.dvb, t.tr[2], T, F, region(c_b1)}, {sv.h1b, t.tr[3], T, d},
-                    {t.dzb1, t.tr[4], T, d, region(c_bo)}, {sv.ctx, t.tr[5], T, d},
-                    {t.dqkv, t.tr[6], T, 3 * d, region(c_bqkv)}, {sv.hb, t.tr[7], T, d}});
+        transposes({{t.dzb, dz2t, T, d, region(c_b2)}, {sv.u, ut, T, F},
+                    {t.dvb, dvt, T, F, region(c_b1)}, {sv.h1b, x1t, T, d},
+                    {dz1, dz1t, T, d, region(c_bo)}, {sv.ctx, ctxt, T, d},
+                    {t.dqkv, dqkvt, T, 3 * d, region(c_bqkv)}, {sv.hb, xt, T, d}});
         finals.push_back({region(c_b2), t.grad + o[9], blocks64, d});
         finals.push_back({region(c_b1), t.grad + o[7], blocks64, F});
         finals.push_back({region(c_bo), t.grad + o[3], blocks64, d});
         finals.push_back({region(c_bqkv), t.grad + o[1], blocks64, 3 * d});
         bwd_gemm("weight gradients", [&] {
-            const GemmJob jobs[4] = {{t.tr[0], t.tr[1], t.grad + o[8], d, F}, {t.tr[2], t.tr[3], t.grad + o[6], F, d},
-                                     {t.tr[4], t.tr[5], t.grad + o[2], d, d}, {t.tr[6], t.tr[7], t.grad + o[0], 3 * d, d}};
+            const GemmJob jobs[4] = {{dz2t, ut, t.grad + o[8], d, F}, {dvt, x1t, t.grad + o[6], F, d},
+                                     {dz1t, ctxt, t.grad + o[2], d, d}, {dqkvt, xt, t.grad + o[0], 3 * d, d}};
             return launch_gemm_group(jobs, 4, T, s, n_cu);
         });
         flush_finals();

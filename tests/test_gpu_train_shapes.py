@@ -5,6 +5,7 @@ an odd number of K tiles in either K order, sequences of one to four blocks with
 and without a remainder.  Every gradient against the fp64 oracle."""
 import numpy as np
 import pytest
+import torch
 
 import paper_2503_05130_amd as ie
 from oracle import train as T
@@ -42,3 +43,19 @@ def test_every_gradient(B, S, d, F, causal):
                 g = tr.export(layer, slot, ie.TRAIN_GRAD, ref.shape)
             assert np.all(np.isfinite(g)), name
             assert rel_l2(g, ref) <= GRAD_REL_L2, (name, rel_l2(g, ref))
+
+
+def test_trainer_memory_per_token():
+    """The weight gradients' operands are transposed into activations that the layer's backward has read: a token
+    takes 141.25 d bytes of a one-layer trainer's workspace and scratch (d_ff = 4 d, 64-wide heads, 128 positions: the forward's workspace 40 d, the layer's saved activations 36 d, the backward's fp32 rows 16 d, its
+    bf16 rows 18 d, two transposed operands 16 d, attention scratch 12 d, column sums 3.25 d)."""
+    d, used = 768, []
+    shape = shape_of(dict(SMALL, n_layers=1, d_model=d, n_heads=d // 64, d_ff=4 * d))
+    for B in (32, 32, 96):   # the first one also allocates what the process keeps
+        torch.cuda.synchronize()
+        before = torch.cuda.mem_get_info()[0]
+        with ie.Trainer(**instance_config(shape, B, 128)):
+            used.append(before - torch.cuda.mem_get_info()[0])
+    per_token = (used[2] - used[1]) / (64 * 128)
+    print(f"trainer bytes {used}: {per_token / d:.1f} d a token", flush=True)
+    assert per_token <= 145 * d, per_token / d
