@@ -74,7 +74,7 @@ hipError_t launch_gemm_group(const GemmJob *jobs, int n_jobs, int K, hipStream_t
 struct GemmPlan {
     bool split_order;   // K >= 2048: even / odd K tiles summed separately, then added
     bool tile_split;    // the chosen tile's order (must equal split_order)
-    int bm, bn;         // output tile, tokens x features (a workgroup may hold two, stacked, that share W copies)
+    int bm, bn;         // output tile of a workgroup, tokens x features
 };
 GemmPlan gemm_plan(int M, int N, int K, int align, int n_cu, bool ln_residual = false);
 

@@ -623,13 +623,13 @@ using E32x64 = Cfg<32, 64, 2, 2, 2, 4, 4, true>;
 using E64x64 = Cfg<64, 64, 2, 2, 2, 4, 4, true>;
 using E64x96 = Cfg<64, 96, 2, 2, 2, 4, 4, true>;
 using E128x64 = Cfg<128, 64, 4, 2, 2, 4, 4, true>;
-using E2x64x96 = Cfg<128, 96, 4, 2, 2, 4, 4, false>;     // two 64 x 96 tiles that share their W copies
+using E128x96 = Cfg<128, 96, 4, 2, 2, 4, 4, false>;
 using E128x128 = Cfg<128, 128, 2, 4, 2, 4, 4, false>;
 using E256x128 = Cfg<256, 128, 4, 2, 2, 3, 3, false>;
 
 enum class Tile {
     S32x32, S32x64, S64x64, S64x96, S128x64, S128x96, S128x96p, S128x128, S128x192, S256x256,
-    E32x32, E32x64, E64x64, E64x96, E128x64, E2x64x96, E128x128, E256x128
+    E32x32, E32x64, E64x64, E64x96, E128x64, E128x96, E128x128, E256x128
 };
 
 // K summation order from the weight shape (N, K) only: K >= 2048 uses the
@@ -643,21 +643,20 @@ struct TileInfo {
     Tile tile;
     bool split;      // K order
     int bm, bn;      // a workgroup's output block
-    int tile_m;      // rows of one tile: bm, or bm / 2 where a workgroup holds two
     int per_cu;      // workgroups whose rings share a CU
     int step;        // relative time of one K tile of one workgroup
 };
 
 constexpr TileInfo kTiles[] = {
-    {Tile::S32x32, false, 32, 32, 32, 4, 51},      {Tile::S32x64, false, 32, 64, 32, 3, 51},
-    {Tile::S64x64, false, 64, 64, 64, 2, 100},     {Tile::S64x96, false, 64, 96, 64, 2, 117},
-    {Tile::S128x64, false, 128, 64, 128, 1, 180},  {Tile::S128x96, false, 128, 96, 128, 1, 172},
-    {Tile::S128x96p, false, 128, 96, 128, 2, 188}, {Tile::S128x128, false, 128, 128, 128, 2, 222},
-    {Tile::S128x192, false, 128, 192, 128, 2, 377}, {Tile::S256x256, false, 256, 256, 256, 1, 1155},
-    {Tile::E32x32, true, 32, 32, 32, 4, 78},       {Tile::E32x64, true, 32, 64, 32, 3, 96},
-    {Tile::E64x64, true, 64, 64, 64, 2, 100},      {Tile::E64x96, true, 64, 96, 64, 2, 130},
-    {Tile::E128x64, true, 128, 64, 128, 1, 168},   {Tile::E2x64x96, true, 128, 96, 64, 1, 169},
-    {Tile::E128x128, true, 128, 128, 128, 1, 264}, {Tile::E256x128, true, 256, 128, 256, 1, 470},
+    {Tile::S32x32, false, 32, 32, 4, 51},      {Tile::S32x64, false, 32, 64, 3, 51},
+    {Tile::S64x64, false, 64, 64, 2, 100},     {Tile::S64x96, false, 64, 96, 2, 117},
+    {Tile::S128x64, false, 128, 64, 1, 180},  {Tile::S128x96, false, 128, 96, 1, 172},
+    {Tile::S128x96p, false, 128, 96, 2, 188}, {Tile::S128x128, false, 128, 128, 2, 222},
+    {Tile::S128x192, false, 128, 192, 2, 377}, {Tile::S256x256, false, 256, 256, 1, 1155},
+    {Tile::E32x32, true, 32, 32, 4, 78},       {Tile::E32x64, true, 32, 64, 3, 96},
+    {Tile::E64x64, true, 64, 64, 2, 100},      {Tile::E64x96, true, 64, 96, 2, 130},
+    {Tile::E128x64, true, 128, 64, 1, 168},   {Tile::E128x96, true, 128, 96, 1, 169},
+    {Tile::E128x128, true, 128, 128, 1, 264}, {Tile::E256x128, true, 256, 128, 1, 470},
 };
 // the same unit: a round's fixed part (launch of its workgroups, first copies, epilogue)
 constexpr long kRoundSequential = 4673, kRoundSplit = 4458;
@@ -757,7 +756,7 @@ hipError_t launch_group(GemmGroup &g, hipStream_t s) {
 
 GemmPlan gemm_plan(int M, int N, int K, int align, int n_cu, bool ln_residual) {
     const TileInfo &t = choose_tile(M, N, K, align, n_cu, !ln_residual);
-    return GemmPlan{split_k_order(N, K), t.split, t.tile_m, t.bn};
+    return GemmPlan{split_k_order(N, K), t.split, t.bm, t.bn};
 }
 
 hipError_t launch_gemm(Epi epi, const bf16_t *a, const bf16_t *w, const bf16_t *bias,
@@ -776,7 +775,7 @@ hipError_t launch_gemm(Epi epi, const bf16_t *a, const bf16_t *w, const bf16_t *
     switch (choose_tile(M, N, K, align, n_cu, epi != Epi::BiasLnResidF32).tile) {
 #define IEFWD_TILES(X) \
     X(S32x32) X(S32x64) X(S64x64) X(S64x96) X(S128x64) X(S128x96) X(S128x96p) X(S128x128) X(S128x192) X(S256x256) \
-    X(E32x32) X(E32x64) X(E64x64) X(E64x96) X(E128x64) X(E2x64x96) X(E128x128) X(E256x128)
+    X(E32x32) X(E32x64) X(E64x64) X(E64x96) X(E128x64) X(E128x96) X(E128x128) X(E256x128)
 #define X(T) case Tile::T: return launch_tile<T>(epi, p, stream);
         IEFWD_TILES(X)
 #undef X

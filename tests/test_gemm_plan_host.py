@@ -76,20 +76,20 @@ def test_skinny_group_count(M, N, K, ln, groups):
 
 
 @pytest.mark.parametrize("M,N,K,n_cu,tile", [
-    # BERT-base batch 32 (4096 tokens): FFN-down (even/odd order), FFN-up, out-projection
-    (4096, 768, 3072, 256, (64, 96)),    # 512 tiles, two per CU
-    (4096, 768, 3072, 192, (128, 128)),  # 64 x 96 would leave some CUs three tiles
-    (4096, 768, 3072, 128, (64, 96)),    # four per CU either way: the first choice stays
-    (4096, 3072, 768, 256, (128, 192)),
-    (4096, 3072, 768, 192, (128, 128)),
-    (4096, 768, 768, 256, (128, 96)),
-    (4096, 768, 768, 192, (128, 128)),
+    # BERT-base batch 32 (4096 tokens): FFN-down (even/odd order), FFN-up, out-projection.  The 128 x 96 tile of
+    # the even/odd order was reported as (64, 96) while a workgroup held two such tiles; it is one tile.
+    (4096, 768, 3072, 256, (128, 96)),   # 256 tiles, one per CU
+    (4096, 768, 3072, 192, (128, 128)),  # 128 x 96 would leave some CUs two tiles, 192 of 128 x 128 fill the share
+    (4096, 768, 3072, 128, (128, 96)),   # two per CU
+    (4096, 3072, 768, 256, (128, 192)),  # 512 tiles, two per CU
+    (4096, 3072, 768, 192, (128, 128)),  # 768 tiles, four per CU, against three of 128 x 192
+    (4096, 768, 768, 256, (128, 96)),    # one per CU
+    (4096, 768, 768, 192, (128, 128)),   # one per CU
     (4096, 2304, 768, 192, (128, 192)),  # QKV: 384 tiles fill 192 CUs twice
 ])
 def test_tile_balances_the_share(M, N, K, n_cu, tile):
-    """On shares whose CU count leaves the first-choice tiles unevenly spread, a
-    128 x 128 tile of the same K order is taken when it leaves the busiest CU
-    with at most 90% of the work."""
+    """The tile with the least estimated time: the busiest CU's workgroups times the K tiles times a tile's
+    measured step time, plus a fixed part for each round of resident workgroups."""
     k_order, tile_order, bm, bn = ie.test_gemm_plan(M, N, K, N, n_cu)
     assert (bm, bn) == tile and k_order == tile_order
 

@@ -28,7 +28,7 @@ pytestmark = pytest.mark.gpu
     ((256, 256), 4000, 4096, 1024), ((256, 256), 4095, 4096, 1088),
     ((32, 32), 33, 64, 2048), ((32, 64), 65, 3072, 2112), ((64, 64), 129, 4096, 2048),
     ((64, 96), 513, 2304, 2112), ((128, 64), 257, 4096, 2112),
-    ((64, 96), 4095, 768, 2112),                                 # two tiles in a workgroup
+    ((128, 96), 4095, 768, 2112),
     ((128, 128), 513, 4096, 2112), ((256, 128), 4097, 1024, 2048), ((256, 128), 2047, 8192, 2112),
 ])
 @pytest.mark.parametrize("epi", [ie.EPI_BIAS_BF16, ie.EPI_BIAS_RESID_F32])

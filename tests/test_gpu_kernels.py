@@ -33,26 +33,26 @@ def gemm_bound(a64, w64, K):
 
 
 @pytest.mark.parametrize("M,N,K", [
-    (64, 384, 128),      # one-layer encoder QKV shape
-    (1, 64, 64),         # single row
-    (37, 192, 128),      # ragged M, 64 x 64 tiles
-    (130, 320, 192),     # ragged M over several tiles
-    (1000, 768, 768),    # 64 x 64 tiles (most tiles), ragged M
+    (64, 384, 128),      # one-layer encoder QKV shape, 32 x 32 tiles
+    (1, 64, 64),         # single row, 32 x 32
+    (37, 192, 128),      # ragged M, 32 x 32
+    (130, 320, 192),     # ragged M over several 32 x 32 tiles
+    (1000, 768, 768),    # 64 x 64, ragged M
     (512, 3072, 768),    # 64 x 96 tiles, 4 waves
     (4096, 3072, 256),   # 128 x 192 tiles, 8 waves
     (4125, 2496, 128),   # 128 x 192 tiles, ragged M
     (4096, 1024, 256),   # 128 x 128 tiles, 8 waves
     (4096, 768, 768),    # 128 x 96 tiles, 8 waves
-    (2000, 1024, 512),   # 64 x 128 tiles, ragged M
-    (300, 1024, 1024),   # 64 x 64 tiles, ragged M
-    (256, 768, 3072),    # long K: split (even/odd) K order, 64 x 96
-    (130, 512, 2048),    # split order, small product: 32 x 64, ragged M
-    (768, 768, 4096),    # split order, small product: 32 x 64 (an out-projection weight gradient)
-    (1000, 1024, 2048),  # split order, small product: 32 x 64, ragged M
-    (2000, 768, 2048),   # split order, 64 x 96, ragged M (just past the small-product limit)
+    (2000, 1024, 512),   # 128 x 64 tiles, ragged M
+    (300, 1024, 1024),   # 32 x 64 tiles, ragged M
+    (256, 768, 3072),    # long K: split (even/odd) K order, 32 x 32
+    (130, 512, 2048),    # split order, 32 x 32, ragged M
+    (768, 768, 4096),    # split order, 64 x 64 (an out-projection weight gradient)
+    (1000, 1024, 2048),  # split order, 64 x 64, ragged M
+    (2000, 768, 2048),   # split order, 64 x 96, ragged M
     (2048, 2048, 2048),  # split order, 128 x 128
-    (4096, 768, 3072),   # split order, 64 x 96 (the BERT-base FFN-down product)
-    (4133, 768, 2048),   # split order, 64 x 96, ragged M
+    (4096, 768, 3072),   # split order, 128 x 96 (the BERT-base FFN-down product)
+    (4133, 768, 2048),   # split order, 128 x 128, ragged M
 ])
 @pytest.mark.parametrize("epi", [ie.EPI_BIAS_BF16, ie.EPI_BIAS_GELU_BF16, ie.EPI_BIAS_RESID_F32])
 def test_gemm_epilogues(M, N, K, epi):
@@ -84,17 +84,19 @@ def test_gemm_epilogues(M, N, K, epi):
     assert np.all(err <= tol), f"max excess at {worst}: err {err[worst]} tol {tol[worst]}"
 
 
-@pytest.mark.parametrize("M,N,K", [
-    (512, 768, 768),      # 64 x 64 tiles throughout
-    (4096, 3072, 768),    # 128 x 192 tiles (8 waves) for the full batch, 64 x 64 / 64 x 96 for the slices
-    (4096, 1024, 4096),   # split K order: 128 x 128 for the full batch, 32 x 64 for the slices
-    (4096, 768, 3072),    # split K order: 64 x 96 for the full batch (the BERT-base FFN-down
-                          # product), 32 x 64 for the slices
-    (2048, 768, 4096),    # split K order: 64 x 96 for the full batch, 32 x 64 for the slices
+@pytest.mark.parametrize("M,N,K,tile,slices", [
+    # the full batch's tile and those of its slices of 1, 37 and 128 rows
+    (512, 768, 768, (32, 64), [(32, 32), (32, 32), (32, 32)]),
+    (4096, 3072, 768, (128, 192), [(32, 32), (32, 32), (32, 64)]),
+    (4096, 1024, 4096, (128, 128), [(32, 32), (32, 32), (32, 32)]),   # split K order from here on
+    (4096, 768, 3072, (128, 96), [(32, 32), (32, 32), (32, 32)]),     # the BERT-base FFN-down product
+    (2048, 768, 4096, (64, 96), [(32, 32), (32, 32), (32, 32)]),
 ])
-def test_gemm_batch_invariance(M, N, K):
+def test_gemm_batch_invariance(M, N, K, tile, slices):
     # rows computed in a large batch equal the same rows computed alone, bit for
     # bit, even when the two launches pick different tile shapes
+    assert ie.test_gemm_plan(M, N, K, N, 256)[2:] == tile
+    assert [ie.test_gemm_plan(m, N, K, N, 256)[2:] for m in (1, 37, 128)] == slices
     a, w, bias, _ = gemm_inputs(M, N, K, seed=3)
     a_d, w_d, b_d = to_dev(a), to_dev(w.t()), to_dev(bias)
     full = torch.empty((M, N), dtype=torch.bfloat16, device=DEV)
