@@ -84,21 +84,21 @@ __device__ inline void dma16(const bf16_t *base, uint32_t off, uint32_t lds) {
 // operations of this wave are outstanding (expcnt left unconstrained).
 constexpr int waitcnt_imm(int vm, int lgkm) { return (vm & 15) | (7 << 4) | ((lgkm & 15) << 8) | ((vm >> 4) << 14); }
 
-// Tile configuration: BM x BN output tile of WGM x WGN waves; A tiles of the
-// K loop in a ring of SA slots, W tiles in one of SW slots, 64 K deep each
+// Tile configuration: BM x BN output tile of WGM x WGN waves; A tiles and W
+// tiles of the K loop in a ring of S slots each, 64 K deep
 // (128-byte rows: whole cache lines).  ORD is the K order: 1 adds the 32-wide
 // K chunks in sequence, 2 adds the 64-wide K tiles of even and of odd index in
 // sequence into an accumulator each, then the two.  AHEAD: a whole K tile's
 // fragments are read one tile ahead instead of half a tile's one half ahead.
-template <int BM_, int BN_, int WGM_, int WGN_, int ORD_, int SA_, int SW_, bool AHEAD_>
+template <int BM_, int BN_, int WGM_, int WGN_, int ORD_, int S_, bool AHEAD_>
 struct Cfg {
-    static constexpr int BM = BM_, BN = BN_, WGM = WGM_, WGN = WGN_, ORD = ORD_, SA = SA_, SW = SW_, BK = 64;
+    static constexpr int BM = BM_, BN = BN_, WGM = WGM_, WGN = WGN_, ORD = ORD_, S = S_, BK = 64;
     static constexpr bool AHEAD = AHEAD_;
     static constexpr int NW = WGM * WGN, NT = 64 * NW;         // waves / threads per workgroup
     static constexpr int TM = BM / WGM, TN = BN / WGN;         // per-wave tile (tokens x features)
     static constexpr int FM = TM / 16, FN = TN / 16;           // 16 x 16 MFMA blocks per wave
     static constexpr int A_SLOT = BM * BK, W_SLOT = BN * BK;   // bf16 elements per ring slot
-    static constexpr int RING = SA * A_SLOT + SW * W_SLOT;
+    static constexpr int RING = S * (A_SLOT + W_SLOT);
     static constexpr int GA = BM / 8, GW = BN / 8;             // 1 KB copies (8 rows) per slot
     static constexpr int DA = GA / NW, DW = (GW + NW - 1) / NW;   // per wave (at most)
     // waves per SIMD the register budget is sized for: as many workgroups as
@@ -108,8 +108,8 @@ struct Cfg {
     static_assert(TM % 16 == 0 && TN % 16 == 0 && BM % 16 == 0 && BN % 16 == 0, "tile");
     static_assert(ORD == 1 || ORD == 2, "K order");
     static_assert(GA % NW == 0, "waves share the A copies evenly");
-    static_assert(SW >= 2 && (SA == SW || (SA == 3 && SW == 2)), "ring slots");
-    static_assert((SA - 1) * (DA + DW) <= 63, "ring depth (vmcnt holds 6 bits)");
+    static_assert(S >= 2, "ring slots");
+    static_assert((S - 1) * (DA + DW) <= 63, "ring depth (vmcnt holds 6 bits)");
 };
 
 // Waits until at most `t` K tiles' worth of this wave's copies (`per` each,
@@ -136,21 +136,21 @@ __device__ inline void wait_tiles(int t, int per) {
 
 template <bool B> struct Flag { static constexpr bool value = B; };
 
-// The main loop over the K tiles through the two rings.  W tile t lives in
-// slot t % SW of its ring, A tile t in slot t % SA.  Step j multiplies tile j
-// as two 32-deep halves:
+// The main loop over the K tiles through the two rings.  Tile t of A and of W
+// lives in slot t % S of its ring.  Step j multiplies tile j as two 32-deep
+// halves:
 //
 //   !AHEAD: read half 1 of tile j; MFMAs of half 0;
 //           wait (my copies of tile j + 1, my LDS reads), barrier: tile j + 1
 //           is visible to all and no wave reads tile j's slots any more;
 //           read half 0 of tile j + 1;
-//           MFMAs of half 1, the copies of W tile j + SW and A tile j + SA
-//           issued between them into the slots tile j left
+//           MFMAs of half 1, the copies of tile j + S issued between them
+//           into the slots tile j left
 //   AHEAD:  the wait and the barrier, read both halves of tile j + 1, then the
 //           MFMAs of tile j with the copies between them
 //
 // so every fragment read has a half tile's (a tile's) MFMAs to hide behind,
-// every copy SA - 1 (SW - 1) tiles' time, and the copies' issue slots fill the
+// every copy S - 1 tiles' time, and the copies' issue slots fill the
 // matrix unit's shadow.
 //
 // What bounds it (4096 tokens): the copies' rate is the bytes in flight over a
@@ -164,9 +164,9 @@ template <bool B> struct Flag { static constexpr bool value = B; };
 template <class C>
 __device__ inline void main_loop(const GemmParams &p, bf16_t *lds, int wave, int lane, int m0, int n0,
                                  f32x4 (&acc)[C::ORD][C::FN][C::FM]) {
-    constexpr int NW = C::NW, DA = C::DA, DW = C::DW, SA = C::SA, SW = C::SW, FM = C::FM, FN = C::FN;
+    constexpr int NW = C::NW, DA = C::DA, DW = C::DW, S = C::S, FM = C::FM, FN = C::FN;
     const int wm = wave % C::WGM, wn = wave / C::WGM;
-    bf16_t *ring_a = lds, *ring_w = ring_a + SA * C::A_SLOT;
+    bf16_t *ring_a = lds, *ring_w = ring_a + S * C::A_SLOT;
 
     // Copy sources of this lane: copy i of this wave moves the 8-row group
     // wave + NW i of a slot; lane l fills row l / 8 of it at chunk position
@@ -193,10 +193,10 @@ __device__ inline void main_loop(const GemmParams &p, bf16_t *lds, int wave, int
     const int per = DA + DW - !w_last;
     auto copy_w = [&](int t, int i) {
         if (i < DW - 1 || w_last)
-            dma16(base_w + t * 64, off_w[i], lds_w + (t % SW) * (C::W_SLOT * 2) + i * NW * 1024);
+            dma16(base_w + t * 64, off_w[i], lds_w + (t % S) * (C::W_SLOT * 2) + i * NW * 1024);
     };
     auto copy_a = [&](int t, int i) {
-        dma16(base_a + t * 64, off_a[i], lds_a + (t % SA) * (C::A_SLOT * 2) + i * NW * 1024);
+        dma16(base_a + t * 64, off_a[i], lds_a + (t % S) * (C::A_SLOT * 2) + i * NW * 1024);
     };
     // fragment rows: lane % 16 of each 16-row block; 16-byte chunk 4 half + lane / 16
     const int ra = wm * C::TM + (lane & 15), rw = wn * C::TN + (lane & 15);
@@ -205,15 +205,15 @@ __device__ inline void main_loop(const GemmParams &p, bf16_t *lds, int wave, int
     };
     auto read = [&](Frag &f, int t, int half) {
         const int c = half * 4 + (lane >> 4);
-        const bf16_t *sa = ring_a + (t % SA) * C::A_SLOT + ra * 64 + ((c ^ swizzle(ra)) * 8);
-        const bf16_t *sw = ring_w + (t % SW) * C::W_SLOT + rw * 64 + ((c ^ swizzle(rw)) * 8);
+        const bf16_t *sa = ring_a + (t % S) * C::A_SLOT + ra * 64 + ((c ^ swizzle(ra)) * 8);
+        const bf16_t *sw = ring_w + (t % S) * C::W_SLOT + rw * 64 + ((c ^ swizzle(rw)) * 8);
 #pragma unroll
         for (int jj = 0; jj < FN; ++jj) f.w[jj] = *reinterpret_cast<const bf16x8 *>(sw + jj * 16 * 64);
 #pragma unroll
         for (int i = 0; i < FM; ++i) f.a[i] = *reinterpret_cast<const bf16x8 *>(sa + i * 16 * 64);
     };
-    // the MFMAs of one half tile; copies [D0, D1) of tile j + SA / j + SW (W's
-    // first) are issued between them
+    // the MFMAs of one half tile; copies [D0, D1) of tile j + S (W's first) are
+    // issued between them
     auto mfma = [&](f32x4 (&c)[FN][FM], const Frag &f, auto copies, auto &&issue, int d0, int d1) {
         constexpr int NM = FN * FM;
 #pragma unroll
@@ -234,49 +234,34 @@ __device__ inline void main_loop(const GemmParams &p, bf16_t *lds, int wave, int
     };
     auto issue_full = [&](int j) {
         return [&, j](int d) {
-            if (d < DW) copy_w(j + SW, d);
-            else copy_a(j + SA, d - DW);
+            if (d < DW) copy_w(j + S, d);
+            else copy_a(j + S, d - DW);
         };
     };
     auto issue_tail = [&](int j) {
         return [&, j](int d) {
-            if (d < DW) {
-                if (j + SW < n) copy_w(j + SW, d);
-            } else if (j + SA < n) {
-                copy_a(j + SA, d - DW);
-            }
+            if (j + S >= n) return;
+            if (d < DW) copy_w(j + S, d);
+            else copy_a(j + S, d - DW);
         };
     };
     auto landed = [&](int j, auto full) {   // my copies of tile j + 1 have landed, my LDS reads have returned
-        if constexpr (SA == SW) {
-            // (a count <= 0: all of them)
-            wait_tiles<DA + DW, SA - 2>(decltype(full)::value ? SA - 2 : min(n, j + SA) - (j + 2), per);
-        } else {   // W(j + 1), then A(j + 2)
-            if (decltype(full)::value || j + 2 < n) __builtin_amdgcn_s_waitcnt(waitcnt_imm(DA, 15));
-            else __builtin_amdgcn_s_waitcnt(waitcnt_imm(0, 15));
-        }
+        // (a count <= 0: all of them)
+        wait_tiles<DA + DW, S - 2>(decltype(full)::value ? S - 2 : min(n, j + S) - (j + 2), per);
         __builtin_amdgcn_s_waitcnt(waitcnt_imm(63, 0));
         __builtin_amdgcn_s_barrier();
         asm volatile("" ::: "memory");   // keep LDS accesses on their side of the barrier
     };
 
 #pragma unroll
-    for (int t = 0; t < SA; ++t) {
-        if (t < n && t < SW)
+    for (int t = 0; t < S; ++t) {
+        if (t >= n) continue;
 #pragma unroll
-            for (int i = 0; i < DW; ++i) copy_w(t, i);
-        if (t < n)
+        for (int i = 0; i < DW; ++i) copy_w(t, i);
 #pragma unroll
-            for (int i = 0; i < DA; ++i) copy_a(t, i);
+        for (int i = 0; i < DA; ++i) copy_a(t, i);
     }
-    // tile 0 has landed
-    if constexpr (SA == SW) {
-        wait_tiles<DA + DW, SA - 1>(min(n, SA) - 1, per);
-    } else {
-        if (n > 2) __builtin_amdgcn_s_waitcnt(waitcnt_imm(2 * DA + DW, 15));
-        else if (n > 1) __builtin_amdgcn_s_waitcnt(waitcnt_imm(DA + DW, 15));
-        else __builtin_amdgcn_s_waitcnt(waitcnt_imm(0, 15));
-    }
+    wait_tiles<DA + DW, S - 1>(min(n, S) - 1, per);   // tile 0 has landed
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
     if constexpr (!C::AHEAD) {
@@ -299,10 +284,10 @@ __device__ inline void main_loop(const GemmParams &p, bf16_t *lds, int wave, int
         };
         int j = 0;
         if constexpr (C::ORD == 1) {
-            for (; j + SA < n; ++j) step(j, acc[0], Flag<true>{});
+            for (; j + S < n; ++j) step(j, acc[0], Flag<true>{});
             for (; j < n; ++j) step(j, acc[0], Flag<false>{});
         } else {
-            for (; j + 1 + SA < n; j += 2) {
+            for (; j + 1 + S < n; j += 2) {
                 step(j, acc[0], Flag<true>{});
                 step(j + 1, acc[1], Flag<true>{});
             }
@@ -334,7 +319,7 @@ __device__ inline void main_loop(const GemmParams &p, bf16_t *lds, int wave, int
             __builtin_amdgcn_sched_barrier(0);
         };
         int j = 0;
-        for (; j + 1 + SA < n; j += 2) {
+        for (; j + 1 + S < n; j += 2) {
             step(j, acc[0], f[0], f[1], Flag<true>{});
             step(j + 1, acc[C::ORD - 1], f[1], f[0], Flag<true>{});
         }
@@ -606,26 +591,26 @@ __global__ __launch_bounds__(C::NT) __attribute__((amdgpu_waves_per_eu(C::WPE)))
 }
 
 // Tile configurations.
-//                   BM   BN  WGM WGN ORD SA SW AHEAD
-using S32x32 = Cfg<32, 32, 2, 2, 1, 5, 5, true>;         // 4 waves
-using S32x64 = Cfg<32, 64, 2, 2, 1, 4, 4, true>;
-using S64x64 = Cfg<64, 64, 2, 2, 1, 4, 4, true>;
-using S64x96 = Cfg<64, 96, 2, 2, 1, 4, 4, true>;
-using S128x64 = Cfg<128, 64, 4, 2, 1, 4, 4, true>;       // 8 waves from here on
-using S128x96 = Cfg<128, 96, 4, 2, 1, 4, 4, false>;      // one workgroup per CU
-using S128x96p = Cfg<128, 96, 4, 2, 1, 2, 2, false>;     // two
-using S128x128 = Cfg<128, 128, 2, 4, 1, 2, 2, false>;
-using S128x192 = Cfg<128, 192, 2, 4, 1, 2, 2, false>;
-using S256x256 = Cfg<256, 256, 2, 4, 1, 2, 2, false>;
+//                   BM   BN  WGM WGN ORD S AHEAD
+using S32x32 = Cfg<32, 32, 2, 2, 1, 5, true>;         // 4 waves
+using S32x64 = Cfg<32, 64, 2, 2, 1, 4, true>;
+using S64x64 = Cfg<64, 64, 2, 2, 1, 4, true>;
+using S64x96 = Cfg<64, 96, 2, 2, 1, 4, true>;
+using S128x64 = Cfg<128, 64, 4, 2, 1, 4, true>;       // 8 waves from here on
+using S128x96 = Cfg<128, 96, 4, 2, 1, 4, false>;      // one workgroup per CU
+using S128x96p = Cfg<128, 96, 4, 2, 1, 2, false>;     // two
+using S128x128 = Cfg<128, 128, 2, 4, 1, 2, false>;
+using S128x192 = Cfg<128, 192, 2, 4, 1, 2, false>;
+using S256x256 = Cfg<256, 256, 2, 4, 1, 2, false>;
 // even / odd K order
-using E32x32 = Cfg<32, 32, 2, 2, 2, 5, 5, true>;
-using E32x64 = Cfg<32, 64, 2, 2, 2, 4, 4, true>;
-using E64x64 = Cfg<64, 64, 2, 2, 2, 4, 4, true>;
-using E64x96 = Cfg<64, 96, 2, 2, 2, 4, 4, true>;
-using E128x64 = Cfg<128, 64, 4, 2, 2, 4, 4, true>;
-using E128x96 = Cfg<128, 96, 4, 2, 2, 4, 4, false>;
-using E128x128 = Cfg<128, 128, 2, 4, 2, 4, 4, false>;
-using E256x128 = Cfg<256, 128, 4, 2, 2, 3, 3, false>;
+using E32x32 = Cfg<32, 32, 2, 2, 2, 5, true>;
+using E32x64 = Cfg<32, 64, 2, 2, 2, 4, true>;
+using E64x64 = Cfg<64, 64, 2, 2, 2, 4, true>;
+using E64x96 = Cfg<64, 96, 2, 2, 2, 4, true>;
+using E128x64 = Cfg<128, 64, 4, 2, 2, 4, true>;
+using E128x96 = Cfg<128, 96, 4, 2, 2, 4, false>;
+using E128x128 = Cfg<128, 128, 2, 4, 2, 4, false>;
+using E256x128 = Cfg<256, 128, 4, 2, 2, 3, false>;
 
 enum class Tile {
     S32x32, S32x64, S64x64, S64x96, S128x64, S128x96, S128x96p, S128x128, S128x192, S256x256,

@@ -126,7 +126,7 @@ hipError_t launch_ln_head(const float *z, const float *gamma, const float *beta,
 // bf16 copy of an fp32 array (round to nearest even); n % 4 == 0.
 hipError_t launch_cast_bf16(const float *x, bf16_t *y, size_t n, hipStream_t stream);
 
-// dst[0 .. n) = src[0 .. n), fp32; either may be pinned host memory.
+// dst[0 .. n) = src[0 .. n), fp32, both 16-byte aligned; either may be pinned host memory.
 hipError_t launch_copy_f32(const float *src, float *dst, size_t n, hipStream_t stream);
 
 // One 64-thread workgroup per entry: out[2g] = XCC id, out[2g+1] = HW_ID register.

@@ -147,10 +147,10 @@ __global__ __launch_bounds__(256) void cast_bf16_kernel(const float *__restrict_
 }
 
 // fp32 copy between device buffers, or between one and pinned host memory.
-// 16-byte accesses where both addresses allow it.
+// 16-byte accesses, then the last n % 4.
 __global__ __launch_bounds__(256) void copy_f32_kernel(const float *__restrict__ src, float *__restrict__ dst,
-                                                       size_t n, size_t n4) {
-    const size_t i = (size_t)blockIdx.x * 256 + threadIdx.x;
+                                                       size_t n) {
+    const size_t i = (size_t)blockIdx.x * 256 + threadIdx.x, n4 = n / 4;
     if (i < n4) reinterpret_cast<f32x4 *>(dst)[i] = reinterpret_cast<const f32x4 *>(src)[i];
     else if (4 * n4 + (i - n4) < n) dst[4 * n4 + (i - n4)] = src[4 * n4 + (i - n4)];
 }
@@ -226,10 +226,9 @@ hipError_t launch_cast_bf16(const float *x, bf16_t *y, size_t n, hipStream_t str
 
 hipError_t launch_copy_f32(const float *src, float *dst, size_t n, hipStream_t stream) {
     if (n == 0) return hipSuccess;
-    // vectors first, then single elements: the last n % 4, or all of them
-    const bool aligned = (reinterpret_cast<uintptr_t>(src) | reinterpret_cast<uintptr_t>(dst)) % 16 == 0;
-    const size_t n4 = aligned ? n / 4 : 0, threads = n4 + (n - 4 * n4);
-    return launch_kernel(copy_f32_kernel, dim3((unsigned)((threads + 255) / 256)), dim3(256), stream, src, dst, n, n4);
+    if ((reinterpret_cast<uintptr_t>(src) | reinterpret_cast<uintptr_t>(dst)) % 16) return hipErrorInvalidValue;
+    const size_t threads = n / 4 + n % 4;
+    return launch_kernel(copy_f32_kernel, dim3((unsigned)((threads + 255) / 256)), dim3(256), stream, src, dst, n);
 }
 
 hipError_t launch_cu_probe(uint32_t *out, int n_groups, hipStream_t stream) {
