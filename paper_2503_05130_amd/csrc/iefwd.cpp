@@ -129,8 +129,12 @@ void validate_config(const iefwd_config &c) {
 
 // Host inputs and outputs up to this size (256 KB) go through pinned buffers
 // of the instance that a copy kernel reads or writes: the runtime's copies of
-// pageable memory cost a wait of their own each (a batch of 2 x 32 x 128 from
-// and to host memory: 96 us with them, 71 us without and with one wait per read).
+// pageable memory cost a wait of their own each.  One layer's call, us, with the
+// runtime's copies / staged: input of 8 KB 90 / 74, 256 KB 97 / 76, 1.5 MB 147 /
+// 141, 3 MB 188 / 207; output of 8 KB 85 / 73, 256 KB 95 / 78, 3 MB 268 / 230.
+// Inputs stop gaining between 1.5 and 3 MB, where the copy kernel's rate over
+// the host link counts; the line lies below that so that an instance pins half a
+// megabyte and not several.
 constexpr size_t kStageFloats = 65536;
 
 struct LayerWeights {
