@@ -441,6 +441,26 @@ int iefwd_test_gemm(uint32_t epilogue, const void *a, const void *w, const void 
                     const float *resid, void *out, uint32_t M, uint32_t N, uint32_t K,
                     void *stream);
 
+/* iefwd_test_gemm with the tile chosen for n_cu CUs (it may change the tile, never
+ * the result) and the epilogues of a post-LN block and of training as well: */
+#define IEFWD_EPI_LN_RESID_F32    4u  /* out f32  [M, N] = LN(resid) + A W^T + b, LN(z) = gamma * ((z - mean) * rstd) + beta */
+#define IEFWD_EPI_F32             5u  /* out f32  [M, N] = A W^T (bias unused) */
+#define IEFWD_EPI_GELU_BWD_BF16   6u  /* out bf16 [M, N] = (A W^T) * GELU'(aux), aux bf16 [M, N] (bias unused) */
+#define IEFWD_EPI_GELU2_BF16      7u  /* out bf16 [M, N] = A W^T + b, out2 bf16 [M, N] = GELU(out) */
+/* stats f32 [M, 2] = {mean, rstd}, gamma and beta f32 [N]; operands that the
+ * epilogue does not use may be NULL. */
+int iefwd_test_gemm_on(uint32_t n_cu, uint32_t epilogue, const void *a, const void *w, const void *bias,
+                       const float *resid, const float *stats, const float *gamma, const float *beta,
+                       const void *aux, void *out, void *out2, uint32_t M, uint32_t N, uint32_t K, void *stream);
+
+/* Up to 4 products out[j] f32 [M[j], N[j]] = A[j] W[j]^T of one K in one launch,
+ * as a training step runs a layer's weight gradients; the arrays are host
+ * arrays of device pointers and sizes.  tile_m x tile_n (may be NULL): the output
+ * tile.  a, w and out NULL: only the tile. */
+int iefwd_test_gemm_group(uint32_t n_cu, uint32_t n_jobs, const void *const *a, const void *const *w,
+                          float *const *out, const uint32_t *M, const uint32_t *N, uint32_t K, uint32_t *tile_m,
+                          uint32_t *tile_n, void *stream);
+
 /* Pure host function: how iefwd_test_gemm and the forward pass run an
  * M x N x K product on a stream with n_cu CUs; ln_residual != 0 for the
  * post-LN residual epilogue (the out-projection and FFN-down of a post-LN
@@ -511,6 +531,10 @@ int iefwd_test_skinny_groups(uint32_t M, uint32_t N, uint32_t K, int ln, uint32_
 int iefwd_test_gemm_qkv(const void *a, const void *w, const void *bias, void *q, void *k,
                         void *vt, uint32_t batch, uint32_t seq, uint32_t d_model,
                         uint32_t n_heads, void *stream);
+
+/* The same with the tile chosen for n_cu CUs. */
+int iefwd_test_gemm_qkv_on(uint32_t n_cu, const void *a, const void *w, const void *bias, void *q, void *k, void *vt,
+                           uint32_t batch, uint32_t seq, uint32_t d_model, uint32_t n_heads, void *stream);
 
 /* ctx bf16 [batch, seq, heads*dh] = softmax(Q K^T / sqrt(dh) [+ causal]) V per
  * (batch, head), from Q, K bf16 [batch, heads, seq, dh] and Vt bf16

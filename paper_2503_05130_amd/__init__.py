@@ -25,6 +25,7 @@ OK, EINVAL, ENODEV, ENOMEM, EHIP, ESTATE, EVERSION = 0, -1, -2, -3, -4, -5, -6
 K_QKV, K_ATTN, K_OUTPROJ, K_FFN1, K_FFN2, K_LN, K_BWD_GEMM, K_BWD, K_OPTIM = range(9)
 TRAIN_MASTER, TRAIN_GRAD, TRAIN_MOMENT1, TRAIN_MOMENT2 = range(4)
 EPI_BIAS_BF16, EPI_BIAS_GELU_BF16, EPI_BIAS_RESID_F32 = 0, 1, 2
+EPI_LN_RESID_F32, EPI_F32, EPI_GELU_BWD_BF16, EPI_GELU2_BF16 = 4, 5, 6, 7
 
 _u32, _u64, _i32, _f32, _vp, _sz = (ctypes.c_uint32, ctypes.c_uint64, ctypes.c_int, ctypes.c_float,
                                     ctypes.c_void_p, ctypes.c_size_t)
@@ -69,6 +70,9 @@ SIGNATURES = {
     "iefwd_last_error": (ctypes.c_char_p, []),
     "iefwd_status_string": (ctypes.c_char_p, [_i32]),
     "iefwd_test_gemm": (_i32, [_u32, _vp, _vp, _vp, _vp, _vp, _u32, _u32, _u32, _vp]),
+    "iefwd_test_gemm_on": (_i32, [_u32, _u32] + [_vp] * 10 + [_u32] * 3 + [_vp]),
+    "iefwd_test_gemm_group": (_i32, [_u32, _u32] + [_vp] * 5 + [_u32] + [ctypes.POINTER(_u32)] * 2 + [_vp]),
+    "iefwd_test_gemm_qkv_on": (_i32, [_u32] + [_vp] * 6 + [_u32] * 4 + [_vp]),
     "iefwd_test_gemm_plan": (_i32, [_u32, _u32, _u32, _u32, _u32, _u32, ctypes.POINTER(_u32), ctypes.POINTER(_u32),
                                      ctypes.POINTER(_u32), ctypes.POINTER(_u32)]),
     "iefwd_test_gemm_skinny": (_i32, [_u32, _vp, _vp, _vp, _vp, _vp, _u32, _u32, _u32, _vp, _vp, _vp, _f32, _vp]),
@@ -326,6 +330,25 @@ def test_gemm(epilogue, a, w, bias, resid, out, M, N, K, stream=None) -> None:
                                  _stream(stream)), "iefwd_test_gemm")
 
 
+def test_gemm_on(n_cu, epilogue, a, w, out, M, N, K, bias=None, resid=None, stats=None, gamma=None, beta=None, aux=None,
+                 out2=None, stream=None) -> None:
+    """test_gemm with the tile chosen for n_cu CUs, and with the epilogues of a post-LN block and of training."""
+    _check(lib().iefwd_test_gemm_on(n_cu, epilogue, _ptr(a), _ptr(w), _ptr(bias), _ptr(resid), _ptr(stats), _ptr(gamma),
+                                    _ptr(beta), _ptr(aux), _ptr(out), _ptr(out2), M, N, K, _stream(stream)),
+           "iefwd_test_gemm_on")
+
+
+def test_gemm_group(n_cu, shapes, K, a=None, w=None, out=None, stream=None) -> tuple[int, int]:
+    """Products [M, K] x [N, K]^T for (M, N) in shapes in one launch (none without operands); the output tile."""
+    n = len(shapes)
+    sizes = [(_u32 * n)(*[s[i] for s in shapes]) for i in (0, 1)]
+    ptrs = [None if t is None else (_vp * n)(*[_ptr(x) for x in t]) for t in (a, w, out)]
+    tile = [_u32(), _u32()]
+    _check(lib().iefwd_test_gemm_group(n_cu, n, *ptrs, *sizes, K, *[ctypes.byref(t) for t in tile], _stream(stream)),
+           "iefwd_test_gemm_group")
+    return tile[0].value, tile[1].value
+
+
 def test_gemm_skinny(epilogue, a, w, bias, resid, out, M, N, K, ln=None, stream=None) -> None:
     """ln: None, or (z, gamma, beta, eps) to take the activations as LayerNorm(z)."""
     z, g, b, eps = ln if ln is not None else (None, None, None, 0.0)
@@ -364,6 +387,12 @@ def test_skinny_groups(M, N, K, ln) -> int:
 def test_gemm_qkv(a, w, bias, q, k, vt, batch, seq, d_model, n_heads, stream=None) -> None:
     _check(lib().iefwd_test_gemm_qkv(_ptr(a), _ptr(w), _ptr(bias), _ptr(q), _ptr(k), _ptr(vt), batch, seq,
                                      d_model, n_heads, _stream(stream)), "iefwd_test_gemm_qkv")
+
+
+def test_gemm_qkv_on(n_cu, a, w, bias, q, k, vt, batch, seq, d_model, n_heads, stream=None) -> None:
+    """test_gemm_qkv with the tile chosen for n_cu CUs."""
+    _check(lib().iefwd_test_gemm_qkv_on(n_cu, _ptr(a), _ptr(w), _ptr(bias), _ptr(q), _ptr(k), _ptr(vt), batch, seq,
+                                        d_model, n_heads, _stream(stream)), "iefwd_test_gemm_qkv_on")
 
 
 def test_attention(q, k, vt, ctx, batch, n_heads, seq, head_dim, causal, stream=None) -> None:

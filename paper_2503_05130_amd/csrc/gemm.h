@@ -77,6 +77,8 @@ struct GemmPlan {
     int bm, bn;         // output tile of a workgroup, tokens x features
 };
 GemmPlan gemm_plan(int M, int N, int K, int align, int n_cu, bool ln_residual = false);
+// The same for launch_gemm_group (jobs' M and N).
+GemmPlan gemm_group_plan(const GemmJob *jobs, int n_jobs, int K, int n_cu);
 
 // Activations given as LayerNorm(z): z fp32 [M, K] rows, gamma / beta fp32 [K].
 struct LnIn {

@@ -744,6 +744,13 @@ GemmPlan gemm_plan(int M, int N, int K, int align, int n_cu, bool ln_residual) {
     return GemmPlan{split_k_order(N, K), t.split, t.bm, t.bn};
 }
 
+GemmPlan gemm_group_plan(const GemmJob *jobs, int n_jobs, int K, int n_cu) {
+    Shape shapes[kMaxGemmGroup];
+    for (int j = 0; j < n_jobs; ++j) shapes[j] = {jobs[j].M, jobs[j].N, jobs[j].N};
+    const TileInfo &t = choose_tile(shapes, n_jobs, K, n_cu);
+    return GemmPlan{split_k_order(0, K), t.split, t.bm, t.bn};
+}
+
 hipError_t launch_gemm(Epi epi, const bf16_t *a, const bf16_t *w, const bf16_t *bias,
                        const float *resid, void *out, int M, int N, int K, const QkvDst *qkv,
                        hipStream_t stream, const LnResid *ln, const bf16_t *aux, int n_cu, bf16_t *out2) {

@@ -1642,6 +1642,59 @@ int iefwd_test_gemm(uint32_t epilogue, const void *a, const void *w, const void 
     });
 }
 
+int iefwd_test_gemm_on(uint32_t n_cu, uint32_t epilogue, const void *a, const void *w, const void *bias,
+                       const float *resid, const float *stats, const float *gamma, const float *beta,
+                       const void *aux, void *out, void *out2, uint32_t M, uint32_t N, uint32_t K, void *stream) {
+    return guarded([&] {
+        if (epilogue > IEFWD_EPI_GELU2_BF16 || epilogue == (uint32_t)Epi::Qkv) fail(IEFWD_EINVAL, "unknown epilogue");
+        const Epi epi = (Epi)epilogue;
+        if (!a || !w || !out) fail(IEFWD_EINVAL, "NULL pointer");
+        if (!bias && epi != Epi::F32 && epi != Epi::GeluBwdBf16) fail(IEFWD_EINVAL, "bias is NULL");
+        if (!resid && (epi == Epi::BiasResidF32 || epi == Epi::BiasLnResidF32)) fail(IEFWD_EINVAL, "resid is NULL");
+        if (epi == Epi::BiasLnResidF32 && (!stats || !gamma || !beta)) fail(IEFWD_EINVAL, "NULL LayerNorm operand");
+        if (epi == Epi::GeluBwdBf16 && !aux) fail(IEFWD_EINVAL, "aux is NULL");
+        if (epi == Epi::BiasGelu2Bf16 && !out2) fail(IEFWD_EINVAL, "out2 is NULL");
+        if (N == 0 || N % 64 || K == 0 || K % 64) fail(IEFWD_EINVAL, "N and K must be positive multiples of 64");
+        if ((uint64_t)M * K >= (1ull << 31) || (uint64_t)N * K >= (1ull << 31)) fail(IEFWD_EINVAL, "too large");
+        if (n_cu == 0 || n_cu > 1024) fail(IEFWD_EINVAL, "n_cu must be in [1, 1024]");
+        const LnResid ln{resid, stats, gamma, beta};
+        hip_check(launch_gemm(epi, (const bf16_t *)a, (const bf16_t *)w, (const bf16_t *)bias, resid, out, (int)M,
+                              (int)N, (int)K, nullptr, (hipStream_t)stream,
+                              epi == Epi::BiasLnResidF32 ? &ln : nullptr, (const bf16_t *)aux, (int)n_cu,
+                              (bf16_t *)out2),
+                  "gemm launch");
+    });
+}
+
+int iefwd_test_gemm_group(uint32_t n_cu, uint32_t n_jobs, const void *const *a, const void *const *w,
+                          float *const *out, const uint32_t *M, const uint32_t *N, uint32_t K, uint32_t *tile_m,
+                          uint32_t *tile_n, void *stream) {
+    return guarded([&] {
+        if (n_jobs == 0 || n_jobs > (uint32_t)kMaxGemmGroup) fail(IEFWD_EINVAL, "n_jobs must be in [1, 4]");
+        if (!M || !N) fail(IEFWD_EINVAL, "NULL pointer");
+        if (K == 0 || K % 64 || K > 65536) fail(IEFWD_EINVAL, "K must be a multiple of 64 in [64, 65536]");
+        if (n_cu == 0 || n_cu > 1024) fail(IEFWD_EINVAL, "n_cu must be in [1, 1024]");
+        const bool run = a || w || out;
+        if (run && (!a || !w || !out)) fail(IEFWD_EINVAL, "NULL pointer");
+        GemmJob jobs[kMaxGemmGroup] = {};
+        for (uint32_t j = 0; j < n_jobs; ++j) {
+            if (M[j] == 0 || N[j] == 0 || N[j] % 64) fail(IEFWD_EINVAL, "need M >= 1 and N a positive multiple of 64");
+            if ((uint64_t)M[j] * K >= (1ull << 31) || (uint64_t)N[j] * K >= (1ull << 31)) fail(IEFWD_EINVAL, "too large");
+            jobs[j].M = (int)M[j];
+            jobs[j].N = (int)N[j];
+            if (!run) continue;
+            if (!a[j] || !w[j] || !out[j]) fail(IEFWD_EINVAL, "NULL pointer");
+            jobs[j].a = (const bf16_t *)a[j];
+            jobs[j].w = (const bf16_t *)w[j];
+            jobs[j].out = out[j];
+        }
+        const GemmPlan p = gemm_group_plan(jobs, (int)n_jobs, (int)K, (int)n_cu);
+        if (tile_m) *tile_m = (uint32_t)p.bm;
+        if (tile_n) *tile_n = (uint32_t)p.bn;
+        if (run) hip_check(launch_gemm_group(jobs, (int)n_jobs, (int)K, (hipStream_t)stream, (int)n_cu), "gemm launch");
+    });
+}
+
 int iefwd_test_gemm_plan(uint32_t M, uint32_t N, uint32_t K, uint32_t align, uint32_t n_cu, uint32_t ln_residual,
                          uint32_t *k_order,
                          uint32_t *tile_order, uint32_t *tile_m, uint32_t *tile_n) {
@@ -1749,18 +1802,25 @@ int iefwd_test_skinny_groups(uint32_t M, uint32_t N, uint32_t K, int ln, uint32_
 
 int iefwd_test_gemm_qkv(const void *a, const void *w, const void *bias, void *q, void *k, void *vt,
                         uint32_t batch, uint32_t seq, uint32_t d_model, uint32_t n_heads, void *stream) {
+    return iefwd_test_gemm_qkv_on(256, a, w, bias, q, k, vt, batch, seq, d_model, n_heads, stream);
+}
+
+int iefwd_test_gemm_qkv_on(uint32_t n_cu, const void *a, const void *w, const void *bias, void *q, void *k, void *vt,
+                           uint32_t batch, uint32_t seq, uint32_t d_model, uint32_t n_heads, void *stream) {
     return guarded([&] {
         if (!a || !w || !bias || !q || !k || !vt) fail(IEFWD_EINVAL, "NULL pointer");
         if (d_model == 0 || d_model % 64 || n_heads == 0 || d_model % n_heads) fail(IEFWD_EINVAL, "bad d_model / n_heads");
         const uint32_t dh = d_model / n_heads;
         if (dh % 8) fail(IEFWD_EINVAL, "head dim must be a multiple of 8");
         if (batch == 0 || seq == 0) fail(IEFWD_EINVAL, "empty batch");
+        if (n_cu == 0 || n_cu > 1024) fail(IEFWD_EINVAL, "n_cu must be in [1, 1024]");
         const uint64_t M = (uint64_t)batch * seq;
         if (M * d_model >= (1ull << 31)) fail(IEFWD_EINVAL, "too large");
         QkvDst qd{(bf16_t *)q, (bf16_t *)k, (bf16_t *)vt, (int)seq, 0, (int)seq, attn_seq_pad((int)seq),
                   (int)n_heads, (int)dh, (int)d_model};
         hip_check(launch_gemm(Epi::Qkv, (const bf16_t *)a, (const bf16_t *)w, (const bf16_t *)bias, nullptr, nullptr,
-                              (int)M, (int)(3 * d_model), (int)d_model, &qd, (hipStream_t)stream),
+                              (int)M, (int)(3 * d_model), (int)d_model, &qd, (hipStream_t)stream, nullptr, nullptr,
+                              (int)n_cu),
                   "qkv gemm launch");
     });
 }

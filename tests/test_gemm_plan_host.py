@@ -103,3 +103,19 @@ def test_ln_residual_epilogue_skips_the_widest_tile(n_cu, plain, ln_residual):
     for flag, want in ((False, plain), (True, ln_residual)):
         k_order, tile_order, bm, bn = ie.test_gemm_plan(4096, 768, 768, 768, n_cu, flag)
         assert (bm, bn) == want and k_order == tile_order == 0
+
+
+def test_launches_reject_bad_arguments():
+    L, p = ie.lib(), 0x1000   # never dereferenced: every call fails validation first
+    ok = dict(n_cu=256, epi=5, a=p, w=p, bias=p, resid=p, stats=p, gamma=p, beta=p, aux=p, out=p, out2=p, M=4, N=64, K=64)
+    for bad in (dict(n_cu=0), dict(epi=3), dict(epi=8), dict(a=None), dict(out=None), dict(N=96), dict(K=32), dict(M=1 << 31),
+                dict(epi=2, resid=None), dict(epi=4, stats=None), dict(epi=6, aux=None), dict(epi=7, out2=None),
+                dict(epi=0, bias=None)):
+        assert L.iefwd_test_gemm_on(*{**ok, **bad}.values(), None) == ie.EINVAL, bad
+    assert L.iefwd_test_gemm_qkv_on(0, p, p, p, p, p, p, 1, 4, 128, 2, None) == ie.EINVAL
+    for args in ((256, [], 64), (256, [(1, 64)] * 5, 64), (256, [(0, 64)], 64), (256, [(1, 96)], 64), (256, [(1, 64)], 65),
+                 (0, [(1, 64)], 64)):
+        with pytest.raises(ie.IefwdError) as e:
+            ie.test_gemm_group(*args)
+        assert e.value.status == ie.EINVAL
+    assert ie.test_gemm_group(1, [(257, 128)], 2048) == (256, 128)

@@ -59,3 +59,21 @@ def test_trainer_memory_per_token():
     per_token = (used[2] - used[1]) / (64 * 128)
     print(f"trainer bytes {used}: {per_token / d:.1f} d a token", flush=True)
     assert per_token <= 145 * d, per_token / d
+
+
+@pytest.mark.parametrize("d,F,group,wide", [(768, 3072, (256, 128), (128, 192)), (512, 2048, (128, 128), (128, 128))])
+def test_every_gradient_of_4096_tokens(d, F, group, wide):
+    """The tiles of a BERT-width step: the four weight gradients' one launch, and the FFN-up and dv products."""
+    B, S = 32, 128
+    assert ie.test_gemm_group(256, [(d, F), (F, d), (d, d), (3 * d, d)], B * S) == group
+    assert ie.test_gemm_plan(B * S, F, d, F, 256)[2:] == wide
+    shape = shape_of(dict(SMALL, n_layers=1, d_model=d, n_heads=d // 64, d_ff=F, causal=0))
+    print(f"train step B={B} S={S} d={d} F={F}", flush=True)
+    x, labels = make_batch(shape, B, S, 811)
+    loss_ref, grads_ref, _ = T.loss_and_grads(T.initial_params(shape), x, labels, shape)
+    with ie.Trainer(**instance_config(shape, B, S)) as tr:
+        tr.step(x, labels)
+        assert abs(tr.loss() - loss_ref) <= LOSS_REL * abs(loss_ref)
+        for layer, slot, name, ref in oracle_tensors(grads_ref, shape):
+            g = tr.export(layer, slot, ie.TRAIN_GRAD, ref.shape)
+            assert np.all(np.isfinite(g)) and rel_l2(g, ref) <= GRAD_REL_L2, (name, rel_l2(g, ref))
