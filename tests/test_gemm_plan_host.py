@@ -118,4 +118,4 @@ def test_launches_reject_bad_arguments():
         with pytest.raises(ie.IefwdError) as e:
             ie.test_gemm_group(*args)
         assert e.value.status == ie.EINVAL
-    assert ie.test_gemm_group(1, [(257, 128)], 2048) == (256, 128)
+    assert ie.test_gemm_group(1, [(256, 128)], 2048) == (256, 128)
