@@ -41,7 +41,7 @@ WORKLOAD = "bert_base_l12_d768_s128"
 # 2.000 + WRITE_SIZE x 1.000 KiB, factors from a 256 MiB device copy in the same runs): L2
 # misses, which the 256 MB MALL may serve without touching HBM.  Valid only for the GEMM
 # source and build flags they were counted on; any other source reports null.
-FFN2_TRAFFIC = {"source_sha256_16": "18608253d3f3474f", "bytes": (37120.6 * 2.0 + 13292.1 * 1.0) * 1024}
+FFN2_TRAFFIC = {"source_sha256_16": "407f0ca975856833", "bytes": (37200.7 * 2.0 + 14668.0 * 1.0) * 1024}
 GEMM_SOURCES = ("paper_2503_05130_amd/csrc/gemm.hip", "paper_2503_05130_amd/csrc/gemm.h", "paper_2503_05130_amd/csrc/gemm_device.h",
                 "paper_2503_05130_amd/csrc/launch.h", "paper_2503_05130_amd/csrc/gelu.h",
                 "paper_2503_05130_amd/build.py")
