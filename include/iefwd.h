@@ -544,13 +544,11 @@ int iefwd_test_attention(const void *q, const void *k, const void *vt, void *ctx
                          uint32_t batch, uint32_t n_heads, uint32_t seq, uint32_t head_dim,
                          int causal, void *stream);
 
-/* Host-only: the (query group, batch * head pair) each workgroup of the
+/* Pure host function: the (query group, batch * head pair) each workgroup of the
  * attention kernel's grid works on, for `pairs` pairs of `groups` groups of 128
- * queries on n_cu CUs.  *grid gets the workgroups; out (NULL, or n = 2 * grid
- * values) gets group and pair of each, -1 for an idle one.  Workgroup i runs on
- * XCD i % 8. */
-int iefwd_test_attention_place(uint32_t pairs, uint32_t groups, int causal, uint32_t n_cu, int32_t *out, size_t n,
-                               uint32_t *grid);
+ * queries on n_cu CUs: n = 2 * pairs * groups values, group and pair of each
+ * workgroup in dispatch order.  Workgroup i runs on XCD i % 8. */
+int iefwd_test_attention_place(uint32_t pairs, uint32_t groups, int causal, uint32_t n_cu, int32_t *out, size_t n);
 
 /* Row LayerNorm of z f32 [rows, d]: out_f32 (may be NULL) and out_bf16 (may be
  * NULL) get gamma * (z - mean) / sqrt(var + eps) + beta. */

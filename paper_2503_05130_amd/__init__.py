@@ -84,7 +84,7 @@ SIGNATURES = {
     "iefwd_test_skinny_groups": (_i32, [_u32, _u32, _u32, _i32, ctypes.POINTER(_u32)]),
     "iefwd_test_gemm_qkv": (_i32, [_vp, _vp, _vp, _vp, _vp, _vp, _u32, _u32, _u32, _u32, _vp]),
     "iefwd_test_attention": (_i32, [_vp, _vp, _vp, _vp, _u32, _u32, _u32, _u32, _i32, _vp]),
-    "iefwd_test_attention_place": (_i32, [_u32, _u32, _i32, _u32, _vp, _sz, ctypes.POINTER(_u32)]),
+    "iefwd_test_attention_place": (_i32, [_u32, _u32, _i32, _u32, _vp, _sz]),
     "iefwd_test_layernorm": (_i32, [_vp, _vp, _vp, _vp, _vp, _u32, _u32, _f32, _vp]),
     "iefwd_test_ln_head": (_i32, [_vp, _vp, _vp, _vp, _vp, _vp, _u32, _u32, _u32, _f32, _vp]),
     "iefwd_test_cu_probe": (_i32, [_vp, _u32, _vp]),
@@ -401,12 +401,9 @@ def test_attention(q, k, vt, ctx, batch, n_heads, seq, head_dim, causal, stream=
 
 
 def test_attention_place(pairs: int, groups: int, causal: bool, n_cu: int = 256) -> np.ndarray:
-    """int32 [grid, 2]: the (query group, batch * head pair) of each workgroup of the attention grid; -1: idle."""
-    grid = _u32()
-    args = (pairs, groups, 1 if causal else 0, n_cu)
-    _check(lib().iefwd_test_attention_place(*args, None, 0, ctypes.byref(grid)), "iefwd_test_attention_place")
-    out = np.empty((grid.value, 2), dtype=np.int32)
-    _check(lib().iefwd_test_attention_place(*args, out.ctypes.data, out.size, ctypes.byref(grid)),
+    """int32 [pairs * groups, 2]: the (query group, batch * head pair) of each workgroup of the attention grid."""
+    out = np.empty((pairs * groups, 2), dtype=np.int32)
+    _check(lib().iefwd_test_attention_place(pairs, groups, 1 if causal else 0, n_cu, out.ctypes.data, out.size),
            "iefwd_test_attention_place")
     return out
 

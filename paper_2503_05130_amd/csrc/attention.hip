@@ -104,7 +104,7 @@ __global__ __launch_bounds__(kThreads) void attention_kernel(
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int half = lane >> 5, col = lane & 31;
     int qgroup, bh;
-    if (!place.at(blockIdx.x, CAUSAL, qgroup, bh)) return;   // uniform over the workgroup
+    place.at(blockIdx.x, blockIdx.y, CAUSAL, qgroup, bh);
     const int qg0 = qgroup * 32 * kWaves;
     const int q0 = qg0 + wave * 32;                      // this wave's first query
     const bf16_t *Qh = Q + (size_t)bh * seq * DH;
@@ -299,7 +299,7 @@ template <int DH, bool CAUSAL>
 hipError_t launch(const bf16_t *q, const bf16_t *k, const bf16_t *vt, bf16_t *ctx, const AttnPlace &place,
                   int n_heads, int seq, int k_rows, int vt_stride, hipStream_t s) {
     const float scale_log2e = 1.4426950408889634f / sqrtf((float)DH);
-    return launch_kernel(attention_kernel<DH, CAUSAL>, dim3(place.grid()), dim3(kThreads), s, q, k, vt, ctx, place,
+    return launch_kernel(attention_kernel<DH, CAUSAL>, dim3(place.n_bh, place.n_groups), dim3(kThreads), s, q, k, vt, ctx, place,
                          n_heads, seq, k_rows, vt_stride, scale_log2e);
 }
 

@@ -1838,22 +1838,16 @@ int iefwd_test_attention(const void *q, const void *k, const void *vt, void *ctx
     });
 }
 
-int iefwd_test_attention_place(uint32_t pairs, uint32_t groups, int causal, uint32_t n_cu, int32_t *out, size_t n,
-                               uint32_t *grid) {
+int iefwd_test_attention_place(uint32_t pairs, uint32_t groups, int causal, uint32_t n_cu, int32_t *out, size_t n) {
     return guarded([&] {
-        if (!grid) fail(IEFWD_EINVAL, "grid is NULL");
-        if (pairs == 0 || pairs > 65535 || groups == 0 || groups > 1024) fail(IEFWD_EINVAL, "pairs must be in [1, 65535], groups in [1, 1024]");
+        if (!out) fail(IEFWD_EINVAL, "out is NULL");
+        if (pairs == 0 || pairs > 65535 || groups == 0 || groups > 1024)
+            fail(IEFWD_EINVAL, "pairs must be in [1, 65535], groups in [1, 1024]");
         if (n_cu == 0 || n_cu > 1024) fail(IEFWD_EINVAL, "n_cu must be in [1, 1024]");
+        if (n != 2 * (size_t)pairs * groups) fail(IEFWD_EINVAL, "n must be 2 * pairs * groups");
         const AttnPlace place = attention_place((int)pairs, (int)groups, (int)n_cu);
-        *grid = (uint32_t)place.grid();
-        if (!out) return;
-        if (n != 2 * (size_t)*grid) fail(IEFWD_EINVAL, "n must be 2 * grid");
-        for (uint32_t i = 0; i < *grid; ++i) {
-            int group = -1, pair = -1;
-            if (!place.at((int)i, causal != 0, group, pair)) group = pair = -1;
-            out[2 * i] = group;
-            out[2 * i + 1] = pair;
-        }
+        for (uint32_t y = 0; y < groups; ++y)
+            for (uint32_t x = 0; x < pairs; ++x, out += 2) place.at((int)x, (int)y, causal != 0, out[0], out[1]);
     });
 }
 
