@@ -26,9 +26,9 @@
 //
 // What bounds it: the softmax's VALU work (32 exponentials a lane and chunk at a
 // quarter rate, then the sums and maxima), and where a CU holds one workgroup
-// the chain from the scores through the maximum to the context.  Hence both
-// 32-key blocks of a chunk side by side up to their exponentials, no rescale
-// where a block raises no maximum, lane exchanges without LDS, and V^T chunks
+// the chain from the scores through the maximum to the context.  Hence a chunk's
+// two blocks side by side where few workgroups share a CU (pair_blocks), no
+// rescale where a block raises no maximum, lane exchanges without LDS, and V^T chunks
 // stored in the fragments' key order.  Measured, before -> after with the
 // placement below: causal 16 heads x 4001 positions 101 -> 74 us, 8 x 16 heads x
 // 512 20.1 -> 15.9, 2 x 16 heads x 1024 of dim 128 36.5 -> 32.2.  Not kept: one
@@ -86,7 +86,7 @@ __device__ inline float scaled(float x, float scale) {
 
 __device__ inline bf16x8 as_bf16x8(u32x4 v) { return __builtin_bit_cast(bf16x8, v); }
 
-template <int DH, bool CAUSAL>
+template <int DH, bool CAUSAL, bool PAIR>
 __global__ __launch_bounds__(kThreads) void attention_kernel(
     const bf16_t *__restrict__ Q, const bf16_t *__restrict__ K, const bf16_t *__restrict__ Vt,
     bf16_t *__restrict__ ctx, AttnPlace place, int n_heads, int seq, int k_rows, int seq_pad, float scale_log2e) {
@@ -187,10 +187,11 @@ __global__ __launch_bounds__(kThreads) void attention_kernel(
         if (c + 1 < n_chunks) gload(c + 1);
         const bf16_t *kb = lds + buf * (K_ELEMS + V_ELEMS);
         const bf16_t *vb = kb + K_ELEMS;
-        // the chunk's first NB 32-key blocks: their products and maxima side by side
-        auto blocks = [&](auto nb) {
+        // NB 32-key blocks of the chunk from block b0 on: their products and maxima
+        // side by side
+        auto blocks = [&](auto nb, int b0) {
             constexpr int NB = decltype(nb)::value;
-            const int k0 = c * kChunk;
+            const int k0 = c * kChunk + 32 * b0;
             // ---- S^T blocks (32 keys x 32 queries)
             f32x16 st[NB];
 #pragma unroll
@@ -202,7 +203,7 @@ __global__ __launch_bounds__(kThreads) void attention_kernel(
 #pragma unroll
                 for (int sb = 0; sb < NB; ++sb) {
                     const bf16x8 kf = as_bf16x8(*reinterpret_cast<const u32x4 *>(
-                        kb + (sb * 32 + col) * K_STRIDE + ks * 16 + half * 8));
+                        kb + ((b0 + sb) * 32 + col) * K_STRIDE + ks * 16 + half * 8));
                     st[sb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf, qf[ks], st[sb], 0, 0, 0);
                 }
             // key of accumulator entry r: k0 + 32 sb + 8 (r / 4) + 4 half + r % 4.  Only the
@@ -260,19 +261,24 @@ __global__ __launch_bounds__(kThreads) void attention_kernel(
                     bf16x8 pf;   // P^T fragment: entries r = 8 j .. 8 j + 7
 #pragma unroll
                     for (int e = 0; e < 8; ++e) pf[e] = (__bf16)st[sb][8 * j + e];
-                    // chunk-local keys 32 sb + 16 j + 4 half + {0..3, 8..11}
+                    // chunk-local keys 32 (b0 + sb) + 16 j + 4 half + {0..3, 8..11}
 #pragma unroll
                     for (int d = 0; d < DB; ++d) {
                         const u32x4 v = *reinterpret_cast<const u32x4 *>(
-                            vb + (d * 32 + col) * kVtStride + 32 * sb + 16 * j + 8 * half);
+                            vb + (d * 32 + col) * kVtStride + 32 * (b0 + sb) + 16 * j + 8 * half);
                         acc[d] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(v), pf, acc[d], 0, 0, 0);
                     }
                 }
             }
         };
         const int left = wave_active ? wave_key_end - c * kChunk : 0;   // wave-uniform
-        if (left > 32) blocks(std::integral_constant<int, 2>{});
-        else if (left > 0) blocks(std::integral_constant<int, 1>{});
+        if constexpr (PAIR) {
+            if (left > 32) blocks(std::integral_constant<int, 2>{}, 0);
+            else if (left > 0) blocks(std::integral_constant<int, 1>{}, 0);
+        } else {
+            if (left > 0) blocks(std::integral_constant<int, 1>{}, 0);
+            if (left > 32) blocks(std::integral_constant<int, 1>{}, 1);
+        }
         if (c + 1 < n_chunks) lstore(buf ^ 1);
         __syncthreads();
     }
@@ -295,12 +301,27 @@ __global__ __launch_bounds__(kThreads) void attention_kernel(
         }
 }
 
+// A chunk's two 32-key blocks side by side, or one after the other: the same
+// bits.  Side by side wins where a CU holds few workgroups and the chain through
+// the maximum is exposed (us side by side / one after the other: 16 heads x 4001
+// causal 74 / 76, 6 x 16 x 1000, three a CU, 31.6 / 32.2, 2 x 16 x 2000 of dim 128
+// 64.6 / 66.7).  At head dim 64 its 144 registers leave room for three
+// workgroups a CU and the other's 121 for four, which wins from there on (7 x 16
+// x 1000 37.7 / 34.4, 16 x 8192 207 / 193, 16 x 4001 on 64 CUs 166 / 156; at dim 128
+// both leave room for two).  Up to 128 positions, two chunks at most, the
+// shorter code is there sooner (7 x 12 x 93 8.0 / 7.1, 8 x 12 x 128 7.9 / 7.3).
+bool pair_blocks(int head_dim, int seq, const AttnPlace &place, int n_cu) {
+    return seq > 128 && (head_dim == 128 || (long)place.n_bh * place.n_groups <= 3L * n_cu);
+}
+
 template <int DH, bool CAUSAL>
 hipError_t launch(const bf16_t *q, const bf16_t *k, const bf16_t *vt, bf16_t *ctx, const AttnPlace &place,
-                  int n_heads, int seq, int k_rows, int vt_stride, hipStream_t s) {
+                  int n_heads, int seq, int k_rows, int vt_stride, int n_cu, hipStream_t s) {
     const float scale_log2e = 1.4426950408889634f / sqrtf((float)DH);
-    return launch_kernel(attention_kernel<DH, CAUSAL>, dim3(place.n_bh, place.n_groups), dim3(kThreads), s, q, k, vt, ctx, place,
-                         n_heads, seq, k_rows, vt_stride, scale_log2e);
+    return launch_kernel(pair_blocks(DH, seq, place, n_cu) ? attention_kernel<DH, CAUSAL, true>
+                                                           : attention_kernel<DH, CAUSAL, false>,
+                         dim3(place.n_bh, place.n_groups), dim3(kThreads), s, q, k, vt, ctx, place, n_heads, seq, k_rows, vt_stride,
+                         scale_log2e);
 }
 
 }  // namespace
@@ -314,11 +335,11 @@ hipError_t launch_attention(const bf16_t *q, const bf16_t *k, const bf16_t *vt, 
     if (k_rows < seq || vt_stride < attn_seq_pad(seq) || vt_stride % 64 != 0) return hipErrorInvalidValue;
     const AttnPlace place = attention_place(batch * n_heads, (seq + 32 * kWaves - 1) / (32 * kWaves), n_cu);
     if (head_dim == 64)
-        return causal ? launch<64, true>(q, k, vt, ctx, place, n_heads, seq, k_rows, vt_stride, stream)
-                      : launch<64, false>(q, k, vt, ctx, place, n_heads, seq, k_rows, vt_stride, stream);
+        return causal ? launch<64, true>(q, k, vt, ctx, place, n_heads, seq, k_rows, vt_stride, n_cu, stream)
+                      : launch<64, false>(q, k, vt, ctx, place, n_heads, seq, k_rows, vt_stride, n_cu, stream);
     if (head_dim == 128)
-        return causal ? launch<128, true>(q, k, vt, ctx, place, n_heads, seq, k_rows, vt_stride, stream)
-                      : launch<128, false>(q, k, vt, ctx, place, n_heads, seq, k_rows, vt_stride, stream);
+        return causal ? launch<128, true>(q, k, vt, ctx, place, n_heads, seq, k_rows, vt_stride, n_cu, stream)
+                      : launch<128, false>(q, k, vt, ctx, place, n_heads, seq, k_rows, vt_stride, n_cu, stream);
     return hipErrorInvalidValue;
 }
 

@@ -19,6 +19,9 @@ pytestmark = pytest.mark.gpu
     (1, 9, 2200, 64),      # 18 groups of 2 heads an XCD: a row of 32 and one of 4
     (1, 17, 1400, 128),    # 11 groups of 3 heads: 32 and 1
     (2, 20, 897, 64),      # 8 groups of 5 heads: 32 and 8
+    (13, 20, 300, 64),     # 780 workgroups: more than three a CU, a chunk's blocks one after the other
+    (12, 20, 500, 64),     # 960
+    (13, 20, 300, 128),    # head dim 128: side by side at any number
 ])
 @pytest.mark.parametrize("causal", [False, True])
 def test_every_query_is_placed_once(B, H, S, dh, causal):
